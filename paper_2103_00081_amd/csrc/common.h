@@ -60,6 +60,19 @@ struct LineFlat {
     double w[LINE_MAXE];
 };
 
+// The same operator for the Q1 strip kernel, by cell: a line through the cell
+// column at (xi, eta) has the element matrix coef (B B^T) x Mz of the bilinear
+// values B at (xi, eta) and the line integrals Mz of a layer.  In scaled Haar
+// coordinates (op_q1s.hip) B becomes (1, px, py, px py) / 4 per corner pattern
+// and Mz the symmetric [a b; b d] of the z pair; the 1/16 is in a, b, d.  Lines of
+// one cell column are chained; a block of nz entries per line, zero outside its
+// range.
+struct LineCell {
+    double px, py, a, b, d;
+    int32_t src;               // line source index (coefficient slot)
+    int32_t next;              // block of the column's next line, or -1
+};
+
 // Per-instance operator descriptor consumed by the apply kernels.
 struct OpDev {
     int32_t nx, ny, nz;        // cells
@@ -90,6 +103,8 @@ struct OpDev {
     const LineEnt *lents;
     const LineCol *lfcol;      // [NX*NY] (Q1) dense per-column rows, or null
     const LineFlat *lflat;
+    const int32_t *lccol;      // [nx*ny] (Q1) first LineCell block of the cell column or -1; null = none
+    const LineCell *lcell;     // [blocks][nz]
     const double *lcoef;       // per line source: dt c_w max(Q,0)/L at t^{n+1}
     const double *xyz;         // general hexahedra: node coordinates [nnode][3]; null on box meshes
     int64_t off;               // offset of the instance in batch node vectors
@@ -161,11 +176,18 @@ struct LevelGeo {              // one instance on one multigrid level
 };
 
 // ------------------------------------------------------------ launchers
-// Operator kernels (op_q1.hip / op_q2.hip / op_hex.hip); degree 3 selects the
-// Q1 kernels of general hexahedra (node coordinates in OpDev::xyz)
+// Operator kernel families: the LDS tile kernels by degree (op_q1.hip,
+// op_q2.hip), those of general hexahedra (op_hex.hip, node coordinates in
+// OpDev::xyz), and the strip kernels of box meshes (op_q1s.hip)
 constexpr int DEGREE_HEX = 3;
+constexpr int Q1_STRIP = 4;
+// Q1 strips: waves per block (side by side along y), owned node columns per
+// block, and cell rows of a wave
+constexpr int Q1S_WAVES = 4;
+constexpr int Q1S_OWNED = 62;
+constexpr int Q1S_ROWS = 2;
 template <typename T>
-void launch_apply(int degree, int field, int epi, bool masked, bool graded, const OpDev *ops, const WorkItem *work,
+void launch_apply(int family, int field, int epi, bool masked, bool graded, const OpDev *ops, const WorkItem *work,
                   int nwork, const T *x, T *y, const EpiArgs<T> &ep, hipStream_t s);
 // Setup kernels, one instance per launch (op is passed by value).
 // Inverse of the diagonal of the symmetric part of the operator (constrained

@@ -189,6 +189,8 @@ struct hts_mesh {
     hts::DBuf<hts::LineEnt> lents;
     hts::DBuf<hts::LineCol> lfcol;           // Q1: rows by column and plane (LineFlat)
     hts::DBuf<hts::LineFlat> lflat;
+    hts::DBuf<int32_t> lccol;                // Q1: the same by cell column (LineCell)
+    hts::DBuf<hts::LineCell> lcell;
     std::vector<hts::SrcDev> line_srcs;      // coefficient sources (instance-local)
     bool has_lineop = false;
     // time-dependent sources per field
@@ -213,11 +215,18 @@ void prepare_mesh(hts_mesh *m);                 // (re)build derived device data
 void forget_batches(hts_mesh *m);               // drop every cached batch that holds m (solve.hip)
 bool is_constrained(const hts_mesh *m, int field, int i, int j, int k);   // host, after prepare_mesh
 OpDev make_op(const hts_mesh *m, int field, bool fp32, double dt, bool steady, bool mass_only);
-// kernel family of a mesh: its degree, or DEGREE_HEX for general hexahedra
-inline int kernel_degree(const hts_mesh *m) { return m->general ? DEGREE_HEX : m->p; }
-int tile_own_x(int degree, int field);          // owned node columns per tile of the operator kernels, x
-int tile_own_y(int degree, int field);          // and y
+// Kernel family of a mesh.  strips: the family for callers whose results may
+// round differently from earlier ones.  The refined mode keeps the tile kernels:
+// its FP32 Krylov solves turn a last-bit change of an operator into 1e-9 of T
+// (whose tolerance is 1e-8), and its time steps stay the same bit for bit.
+inline int kernel_family(const hts_mesh *m, bool strips)
+{
+    if (m->general) return DEGREE_HEX;
+    return strips && m->p == 1 ? Q1_STRIP : m->p;
+}
+// tiles per node plane of a kernel family along x and y
+void tile_grid(const hts_mesh *m, int family, int field, int &ntx, int &nty);
 // node planes per work item of the operator kernels (force > 0: that depth)
-int zc_for(const hts_mesh *M, int field, int prec, int64_t tiles, int force);
+int zc_for(const hts_mesh *M, int family, int field, int prec, int64_t tiles, int force);
 
 }  // namespace hts

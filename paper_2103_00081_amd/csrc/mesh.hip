@@ -221,6 +221,10 @@ static void build_line_operator(hts_mesh *m)
     m->line_srcs.clear();
     // (column, k) -> (col node, src) -> w
     std::map<std::pair<int64_t, int>, std::map<std::pair<int64_t, int>, double>> rows;
+    // Q1: the same by cell column, blocks of nz entries chained per column
+    std::vector<int32_t> lccol;
+    std::vector<LineCell> lcell;
+    if (p == 1) lccol.assign((size_t)m->n[0] * m->n[1], -1);
     for (const LineSpec &ln : m->lines) {
         if (ln.kind != HTS_LINE_WELL) continue;
         SrcDev s{};
@@ -236,6 +240,18 @@ static void build_line_operator(hts_mesh *m)
         basis1(p, eta, By);
         double gx[3], gw[3];
         gauss(n1, gx, gw);
+        LineCell *blk = nullptr;
+        if (p == 1) {
+            LineCell z{};
+            z.px = std::sqrt(3.0) * (1.0 - 2.0 * xi);
+            z.py = std::sqrt(3.0) * (1.0 - 2.0 * eta);
+            z.src = sid;
+            int32_t &head = lccol[(size_t)cx + (size_t)m->n[0] * cy];
+            z.next = head;
+            head = (int32_t)(lcell.size() / m->n[2]);
+            lcell.resize(lcell.size() + m->n[2], z);
+            blk = &lcell[lcell.size() - m->n[2]];
+        }
         for (const Seg &sg : segments(m, ln.z0, ln.z1)) {
             double zlo = m->cell_lo(2, sg.cz), hz = m->cell_h(2, sg.cz);
             double Mz[3][3] = {{0}};
@@ -245,6 +261,12 @@ static void build_line_operator(hts_mesh *m)
                 basis1(p, (z - zlo) / hz, Bz);
                 for (int s1 = 0; s1 < n1; s1++)
                     for (int t1 = 0; t1 < n1; t1++) Mz[s1][t1] += gw[q] * (sg.b - sg.a) * Bz[s1] * Bz[t1];
+            }
+            if (p == 1) {
+                LineCell &e = blk[sg.cz];
+                e.a += (Mz[0][0] + 2.0 * Mz[0][1] + Mz[1][1]) / 64.0;
+                e.b += std::sqrt(3.0) * (Mz[0][0] - Mz[1][1]) / 64.0;
+                e.d += 3.0 * (Mz[0][0] - 2.0 * Mz[0][1] + Mz[1][1]) / 64.0;
             }
             for (int az = 0; az < n1; az++)
                 for (int ay = 0; ay < n1; ay++)
@@ -266,6 +288,7 @@ static void build_line_operator(hts_mesh *m)
     if (!m->has_lineop) {
         m->lcol.release(); m->lrows.release(); m->lents.release();
         m->lfcol.release(); m->lflat.release();
+        m->lccol.release(); m->lcell.release();
         return;
     }
     std::vector<int32_t> lcol((size_t)m->N[0] * m->N[1], -1);
@@ -334,6 +357,10 @@ static void build_line_operator(hts_mesh *m)
             m->lfcol.upload(&m->alloc, hdr, m->stream);
             m->lflat.upload(&m->alloc, flat, m->stream);
         }
+    }
+    if (p == 1) {
+        m->lccol.upload(&m->alloc, lccol, m->stream);
+        m->lcell.upload(&m->alloc, lcell, m->stream);
     }
     LineRow sent{};
     sent.col = -1;
@@ -458,6 +485,8 @@ OpDev make_op(const hts_mesh *m, int field, bool fp32, double dt, bool steady, b
     o.lents = m->lents.p;
     o.lfcol = (o.lcol && m->lfcol.p) ? m->lfcol.p : nullptr;
     o.lflat = m->lflat.p;
+    o.lccol = o.lcol ? m->lccol.p : nullptr;
+    o.lcell = m->lcell.p;
     o.lcoef = nullptr;
     o.xyz = m->general ? m->xyz.p : nullptr;
     {

@@ -15,7 +15,7 @@
 namespace hts {
 hts_status guard_call(const std::function<void()> &f);
 template <typename T>
-void launch_apply(int degree, int field, int epi, bool masked, bool graded, const OpDev *ops, const WorkItem *work,
+void launch_apply(int family, int field, int epi, bool masked, bool graded, const OpDev *ops, const WorkItem *work,
                   int nwork, const T *x, T *y, const EpiArgs<T> &ep, hipStream_t s);
 
 namespace {
@@ -118,9 +118,10 @@ extern "C" hts_status hts_apply_operator_noalloc(hts_mesh *m, hts_field field, h
         const hipStream_t s = m->stream;
         const bool fp32 = prec == HTS_FP32;
         const bool steady = field == 0 && (dt <= 0.0 || m->B <= 0.0);
-        const int ox = tile_own_x(kernel_degree(m), field), oy = tile_own_y(kernel_degree(m), field);
-        const int ntx = (m->N[0] + ox - 1) / ox, nty = (m->N[1] + oy - 1) / oy;
-        const int zc = zc_for(m, field, fp32 ? 1 : 0, (int64_t)ntx * nty, 0);
+        const int family = kernel_family(m, true);
+        int ntx, nty;
+        tile_grid(m, family, field, ntx, nty);
+        const int zc = zc_for(m, family, field, fp32 ? 1 : 0, (int64_t)ntx * nty, 0);
         const int64_t nzc = (m->N[2] + zc - 1) / zc;
         const int64_t nwork = (int64_t)ntx * nty * nzc;
         const int nsrc = field == 1 ? (int)m->line_srcs.size() : 0;
@@ -186,11 +187,11 @@ extern "C" hts_status hts_apply_operator_noalloc(hts_mesh *m, hts_field field, h
         }
         if (!fp32) {
             EpiArgs<double> ep{};
-            launch_apply<double>(kernel_degree(m), field, EPI_STORE, true, m->graded, ops, work, (int)nwork,
+            launch_apply<double>(family, field, EPI_STORE, true, m->graded, ops, work, (int)nwork,
                                  static_cast<const double *>(x_dev), static_cast<double *>(y_dev), ep, s);
         } else {
             EpiArgs<float> ep{};
-            launch_apply<float>(kernel_degree(m), field, EPI_STORE, true, m->graded, ops + 1, work, (int)nwork,
+            launch_apply<float>(family, field, EPI_STORE, true, m->graded, ops + 1, work, (int)nwork,
                                 static_cast<const float *>(x_dev), static_cast<float *>(y_dev), ep, s);
         }
     });

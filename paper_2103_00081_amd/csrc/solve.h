@@ -13,7 +13,7 @@ namespace hts {
 
 
 template <typename T>
-void launch_apply(int degree, int field, int epi, bool masked, bool graded, const OpDev *ops, const WorkItem *work,
+void launch_apply(int family, int field, int epi, bool masked, bool graded, const OpDev *ops, const WorkItem *work,
                   int nwork, const T *x, T *y, const EpiArgs<T> &ep, hipStream_t s);
 void launch_inv_diag(const OpDev &op, double *inv_diag, hipStream_t s);
 void launch_q1_stencil(const OpDev &op, double *S, hipStream_t s);
@@ -96,15 +96,24 @@ struct Batch {
     int nch = 0;
     DBuf<int32_t> chp;
     RedCtx rch{};
-    // fine-level work lists per field and precision (index [field][prec],
-    // prec 0 FP64, 1 FP32: the z-chunk depth is tuned per field and
-    // precision)
-    std::vector<WorkItem> hwork[2][2];
-    DBuf<WorkItem> work[2][2];
-    int nwork[2][2] = {{0, 0}, {0, 0}};
-    DBuf<int32_t> wkp[2][2];
-    RedCtx rwk[2][2]{};
+    // fine-level work lists by kernel choice (0 tiles, 1 strips where the
+    // meshes have them), field and precision (0 FP64, 1 FP32; the z-chunk
+    // depth is tuned for each)
+    struct WorkSet {
+        DBuf<WorkItem> work;
+        int n = 0;
+        DBuf<int32_t> kp;
+        RedCtx red{};
+    };
+    WorkSet ws[2][2][2];
+    bool strips = false;       // kernel choice of the current call (use_strips on entry)
     int zc_force[2][2] = {{0, 0}, {0, 0}};
+    int family() const { return kernel_family(m[0], strips); }
+    template <typename T>
+    const WorkSet &work_set(int field) const
+    {
+        return ws[strips][field][sizeof(T) == 4];
+    }
 
     DBuf<double> S;
     DBuf<int32_t> active;
@@ -185,8 +194,8 @@ struct Batch {
     void replay(const std::string &key, const std::function<void()> &body);
 
     ~Batch();
-    int pick_zc(int field, int prec, const hts_mesh *M, int64_t tiles) const;
-    void build_work();
+    void build_work(int kind);
+    void use_strips(bool allowed);
     void make_tables(Tables &t, int field, double dt, bool steady, bool mass_only);
     Tables &apply_tables(int field, double dt, bool steady)
     {
@@ -258,8 +267,8 @@ void nn_precondition(hts_nn *nn, Batch &B, int inst, const double *r, double *z,
 void nn_prepare(hts_nn *nn, Batch &B);
 uint64_t nn_serial(const hts_nn *nn);
 // tuned z-chunk depth of the fine operator kernels (0 = none recorded)
-int tuned_zc(int degree, int field, int prec, int NX, int NY, int NZ);
-void set_tuned_zc(int degree, int field, int prec, int NX, int NY, int NZ, int zc);
+int tuned_zc(int family, int field, int prec, int NX, int NY, int NZ);
+void set_tuned_zc(int family, int field, int prec, int NX, int NY, int NZ, int zc);
 void save_tuning();
 std::shared_ptr<Batch> solo_batch(hts_mesh *m);
 // cached batch of several meshes (same meshes, same order)

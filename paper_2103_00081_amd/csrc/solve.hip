@@ -78,8 +78,9 @@ void Batch::drop_graphs()
 // Run body's launches as one graph: captured on first use on a private
 // stream (the caller's stream may be the legacy default stream, which
 // cannot be captured), then replayed on the batch stream.
-void Batch::replay(const std::string &key, const std::function<void()> &body)
+void Batch::replay(const std::string &name, const std::function<void()> &body)
 {
+    const std::string key = name + (strips ? "|s" : "|t");   // the operator kernels captured
     if (!cap) {
         HTS_HIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
     }
@@ -111,16 +112,16 @@ void Batch::replay(const std::string &key, const std::function<void()> &body)
 }
 
 // ----------------------------------------------------------- tuning cache
-// z-chunk depth per (degree, field, node dims), filled by hts_autotune and
+// z-chunk depth per (kernel family, field, precision, node dims), filled by hts_autotune and
 // optionally kept in the JSON file named by HTS_TUNE_CACHE.
 namespace {
 std::map<std::string, int> g_tune;
 bool g_tune_loaded = false;
 
-std::string tune_key(int degree, int field, int prec, int NX, int NY, int NZ)
+std::string tune_key(int family, int field, int prec, int NX, int NY, int NZ)
 {
     char b[96];
-    snprintf(b, sizeof(b), "q%d_f%d_%s_%dx%dx%d", degree, field, prec ? "fp32" : "fp64", NX, NY, NZ);
+    snprintf(b, sizeof(b), "q%d_f%d_%s_%dx%dx%d", family, field, prec ? "fp32" : "fp64", NX, NY, NZ);
     return b;
 }
 
@@ -164,61 +165,74 @@ void tune_save()
 }
 }  // namespace
 
-void set_tuned_zc(int degree, int field, int prec, int NX, int NY, int NZ, int zc)
+void set_tuned_zc(int family, int field, int prec, int NX, int NY, int NZ, int zc)
 {
     tune_load();
-    g_tune[tune_key(degree, field, prec, NX, NY, NZ)] = zc;
+    g_tune[tune_key(family, field, prec, NX, NY, NZ)] = zc;
 }
 
 void save_tuning() { tune_save(); }
 
-int tuned_zc(int degree, int field, int prec, int NX, int NY, int NZ)
+int tuned_zc(int family, int field, int prec, int NX, int NY, int NZ)
 {
     tune_load();
-    auto it = g_tune.find(tune_key(degree, field, prec, NX, NY, NZ));
+    auto it = g_tune.find(tune_key(family, field, prec, NX, NY, NZ));
     return it == g_tune.end() ? 0 : it->second;
 }
 
-// Q1: wide tiles for the pressure operator, narrow ones for the heat operator
-// (degree: the kernel family; general hexahedra use the narrow tiles)
-int tile_own_x(int degree, int field) { return degree == 2 ? 30 : (field == 0 && degree == 1 ? 31 : 15); }
-int tile_own_y(int degree, int field) { return degree == 2 ? 30 : 15; }
+// Q1 strips: Q1S_OWNED of the node columns of the y bands laid end to end (one
+// empty column after each band).  Tiles: Q1 wide for the pressure operator and
+// narrow for the heat operator and general hexahedra, Q2 30 x 30.
+void tile_grid(const hts_mesh *m, int family, int field, int &ntx, int &nty)
+{
+    if (family == Q1_STRIP) {
+        const int own = Q1S_WAVES * Q1S_ROWS - 1;
+        const int64_t cols = (int64_t)((m->N[1] + own - 1) / own) * (m->N[0] + 1);
+        ntx = (int)((cols + Q1S_OWNED - 1) / Q1S_OWNED);
+        nty = 1;
+        return;
+    }
+    const int ox = family == 2 ? 30 : (field == 0 && family == 1 ? 31 : 15), oy = family == 2 ? 30 : 15;
+    ntx = (m->N[0] + ox - 1) / ox;
+    nty = (m->N[1] + oy - 1) / oy;
+}
 
-// work-list / tuning index of an operand type: 0 FP64, 1 FP32
-template <typename T>
-constexpr int prec_of() { return std::is_same<T, double>::value ? 0 : 1; }
-
-int zc_for(const hts_mesh *M, int field, int prec, int64_t tiles, int force)
+int zc_for(const hts_mesh *M, int family, int field, int prec, int64_t tiles, int force)
 {
     const int NZ = M->N[2];
     // Q2 work items start on even node planes (cell-layer boundaries)
     auto fit = [&](int z) { return M->p == 2 ? std::max(2, (std::min(z, NZ) + 1) / 2 * 2) : std::min(z, NZ); };
     if (force > 0) return fit(force);
-    const int t = tuned_zc(kernel_degree(M), field, prec, M->N[0], M->N[1], NZ);
+    const int t = tuned_zc(family, field, prec, M->N[0], M->N[1], NZ);
     if (t > 0) return fit(t);
+    if (family == Q1_STRIP) {
+        // about 1000 blocks, four for each CU.  Small grids: the shortest
+        // march (48^3 heat FP32: 9.5 us at depth 2, 13 at 4); large ones: at
+        // 256 x 256 x 128 depths 8 to 17 are within 5 % of each other, 26 and
+        // more up to 40 % slower
+        return fit((int)std::min<int64_t>(16, std::max<int64_t>(2, (tiles * NZ + 512) / 1024)));
+    }
     // enough blocks to fill 256 CUs several times over
     int64_t z = std::max<int64_t>(4, (tiles * NZ) / 2048);
     z = std::min<int64_t>(z, 32);
     return fit((int)z);
 }
 
-int Batch::pick_zc(int field, int prec, const hts_mesh *M, int64_t tiles) const
-{
-    return zc_for(M, field, prec, tiles, zc_force[field][prec]);
-}
-
-void Batch::build_work()
+// Work lists of the kernel choice `kind` (their blocks depend on the tuning)
+void Batch::build_work(int kind)
 {
     drop_graphs();
+    int64_t mw = std::max<int64_t>(nch, (int64_t)partial.n / 64 - 1);
     for (int f = 0; f < 2; f++)
     for (int pr = 0; pr < 2; pr++) {
+        WorkSet &W = ws[kind][f][pr];
         std::vector<WorkItem> nat;
         for (int i = 0; i < n; i++) {
             hts_mesh *M = m[i];
-            // owned node columns per tile along x and y
-            const int ox = tile_own_x(kernel_degree(M), f), oy = tile_own_y(kernel_degree(M), f);
-            const int tx = (M->N[0] + ox - 1) / ox, ty = (M->N[1] + oy - 1) / oy;
-            const int zc = pick_zc(f, pr, M, (int64_t)tx * ty);
+            const int fam = kernel_family(M, kind == 1);
+            int tx, ty;
+            tile_grid(M, fam, f, tx, ty);
+            const int zc = zc_for(M, fam, f, pr, (int64_t)tx * ty, zc_force[f][pr]);
             for (int z0 = 0; z0 < M->N[2]; z0 += zc)
                 for (int y = 0; y < ty; y++)
                     for (int x = 0; x < tx; x++) {
@@ -231,26 +245,32 @@ void Batch::build_work()
         // XCD-aware order: block b is dispatched to XCD b % 8; give each XCD a
         // contiguous run of neighbouring tiles so halos stay in its L2.
         const int64_t T = (int64_t)nat.size(), per = (T + 7) / 8;
-        hwork[f][pr].clear();
+        std::vector<WorkItem> order;
         for (int64_t b = 0; b < 8 * per; b++) {
             int64_t idx = (b % 8) * per + b / 8;
-            if (idx < T) hwork[f][pr].push_back(nat[idx]);
+            if (idx < T) order.push_back(nat[idx]);
         }
-        nwork[f][pr] = (int)hwork[f][pr].size();
-        work[f][pr].upload(al, hwork[f][pr], s);
+        W.n = (int)order.size();
+        W.work.upload(al, order, s);
         // a block writes its partial sum at the tile's natural index, so the
         // partials of an instance are contiguous and reduced in natural tile
         // order: a batched instance sums exactly like the same instance alone
         std::vector<int32_t> sp(n + 1, 0);
         for (const WorkItem &w : nat) sp[w.inst + 1]++;
         for (int i = 0; i < n; i++) sp[i + 1] += sp[i];
-        wkp[f][pr].upload(al, sp, s);
-        rwk[f][pr] = RedCtx{wkp[f][pr].p, n, n == 1 ? sp[1] : -1};
+        W.kp.upload(al, sp, s);
+        W.red = RedCtx{W.kp.p, n, n == 1 ? sp[1] : -1};
+        mw = std::max<int64_t>(mw, W.n);
     }
-    int64_t mw = nch;
-    for (int f = 0; f < 2; f++)
-        for (int pr = 0; pr < 2; pr++) mw = std::max<int64_t>(mw, nwork[f][pr]);
     partial.alloc(al, (size_t)mw * 64 + 64);
+}
+
+// Kernel choice of the calls that follow: strips where the meshes have them and
+// `allowed`; its work lists are built on first use.
+void Batch::use_strips(bool allowed)
+{
+    strips = allowed && kernel_family(m[0], true) != kernel_family(m[0], false);
+    if (ws[strips][0][0].n == 0) build_work(strips);
 }
 
 std::shared_ptr<Batch> build_batch(const std::vector<hts_mesh *> &ms)
@@ -292,7 +312,6 @@ std::shared_ptr<Batch> build_batch(const std::vector<hts_mesh *> &ms)
     B->ch.upload(al, B->hch, s);
     B->chp.upload(al, sp, s);
     B->rch = RedCtx{B->chp.p, n, n == 1 ? sp[1] : -1};
-    B->build_work();
 
     B->S.alloc(al, (size_t)n * NSLOT);
     B->S.zero(s);
@@ -530,10 +549,9 @@ static double apply_flops(int field, int p, int64_t cells)
 template <typename T>
 void Batch::fine_apply(int field, const OpDev *ops, int epi, bool masked, const T *x, T *y, const EpiArgs<T> &ep)
 {
-    constexpr int pr = std::is_same<T, double>::value ? 0 : 1;
+    const WorkSet &W = work_set<T>(field);
     if (!g_timing.on) {
-        launch_apply<T>(general ? DEGREE_HEX : p, field, epi, masked, graded, ops, work[field][pr].p,
-                        nwork[field][pr], x, y, ep, s);
+        launch_apply<T>(family(), field, epi, masked, graded, ops, W.work.p, W.n, x, y, ep, s);
         return;
     }
     TimingRec r{};
@@ -544,8 +562,7 @@ void Batch::fine_apply(int field, const OpDev *ops, int epi, bool masked, const 
     r.bytes = apply_bytes(field, epi, ntot, ctot, sizeof(T));
     r.flops = apply_flops(field, p, ctot);
     HTS_HIP(hipEventRecord(r.a, s));
-    launch_apply<T>(general ? DEGREE_HEX : p, field, epi, masked, graded, ops, work[field][pr].p, nwork[field][pr], x,
-                    y, ep, s);
+    launch_apply<T>(family(), field, epi, masked, graded, ops, W.work.p, W.n, x, y, ep, s);
     HTS_HIP(hipEventRecord(r.b, s));
     g_timing.recs.push_back(r);
 }
@@ -1181,6 +1198,7 @@ void Batch::build_hierarchy(Hier &H, const hts_solver_opts &o)
                     q1.nnode = ccnt[i];
                     q1.lcol = nullptr;
                     q1.lfcol = nullptr;
+                    q1.lccol = nullptr;
                     q1.dcol = nullptr;
                     const std::vector<int32_t> &fd = m[i]->h_dcol[H.field];
                     if (!fd.empty()) {
@@ -1370,7 +1388,7 @@ int Batch::cg(const Tables &A, const std::function<void(const T *, T *)> &M, con
         vreduce(rch, partial.p, 2, RED_CG_INIT, 0, S.p, active.p, maxit, 0.0, nullptr, s);
     } else {
         apply_op<T>(A, EPI_RESID_NORM, true, x, r, ep);
-        vreduce(rwk[A.field][prec_of<T>()], partial.p, 1, RED_CG_INIT, 0, S.p, active.p, maxit, 0.0, nullptr, s);
+        vreduce(work_set<T>(A.field).red, partial.p, 1, RED_CG_INIT, 0, S.p, active.p, maxit, 0.0, nullptr, s);
     }
     const bool hook = std::is_same<T, double>::value && cg_hook;
     const bool graphed = use_graph && !hook && !g_timing.on;
@@ -1421,7 +1439,7 @@ int Batch::cg(const Tables &A, const std::function<void(const T *, T *)> &M, con
                     EpiArgs<T> e2{};
                     e2.partial = partial.p;
                     apply_op<T>(A, EPI_DOT, true, pv, q, e2);
-                    vreduce(rwk[A.field][prec_of<T>()], partial.p, 1, RED_CG_ALPHA, 0, S.p, active.p, 0, 0.0, nullptr, s);
+                    vreduce(work_set<T>(A.field).red, partial.p, 1, RED_CG_ALPHA, 0, S.p, active.p, 0, 0.0, nullptr, s);
                     vcg_update<T>(vg, x, r, pv, q, ro, partial.p);
                     vreduce(rch, partial.p, 2, RED_CG_CONV, 0, S.p, active.p, maxit, 0.0, nullptr, s);
                 }
@@ -1445,7 +1463,7 @@ int Batch::cg(const Tables &A, const std::function<void(const T *, T *)> &M, con
         EpiArgs<T> e2{};
         e2.partial = partial.p;
         apply_op<T>(A, EPI_DOT, true, pv, q, e2);
-        vreduce(rwk[A.field][prec_of<T>()], partial.p, 1, RED_CG_ALPHA, 0, S.p, active.p, 0, 0.0, nullptr, s);
+        vreduce(work_set<T>(A.field).red, partial.p, 1, RED_CG_ALPHA, 0, S.p, active.p, 0, 0.0, nullptr, s);
         vcg_update<T>(v, x, r, pv, q, ro, partial.p);
         if (hook) cg_hook(reinterpret_cast<const double *>(x), it);
         vreduce(rch, partial.p, 2, RED_CG_CONV, 0, S.p, active.p, maxit, 0.0, nullptr, s);
@@ -1487,7 +1505,7 @@ void Batch::fgmres(const Tables &A, const std::function<void(const T *, T *)> &M
             vreduce(rch, partial.p, 2, RED_STORE, S_RR, S.p, active.p, 0, 0.0, nullptr, s);
         } else {
             apply_op<T>(A, EPI_RESID_NORM, true, x, V, ep);
-            vreduce(rwk[A.field][prec_of<T>()], partial.p, 1, RED_STORE, S_RR, S.p, active.p, 0, 0.0, nullptr, s);
+            vreduce(work_set<T>(A.field).red, partial.p, 1, RED_STORE, S_RR, S.p, active.p, 0, 0.0, nullptr, s);
         }
         // which instances take part (S_CYC) is read back with the first
         // check of the Arnoldi steps, not on its own
@@ -1643,7 +1661,7 @@ FieldStats Batch::solve_field(int field, Hier *mg, const Tables &A, double *b64,
         ep.b = b64;
         ep.partial = partial.p;
         apply_op<double>(A, EPI_RESID_NORM, true, x64, this->y.p, ep);
-        vreduce(rwk[A.field][0], partial.p, 1, RED_NONE, 0, S.p, active.p, 0, 0.0, redout.p, s);
+        vreduce(work_set<double>(A.field).red, partial.p, 1, RED_NONE, 0, S.p, active.p, 0, 0.0, redout.p, s);
         outer_check(n, active.p, S.p, redout.p, s);
         HTS_HIP(hipEventRecord(e1, s));
         // The first check is read back with the inner solve's last export
@@ -1770,7 +1788,7 @@ FieldStats Batch::solve_field(int field, Hier *mg, const Tables &A, double *b64,
         if (stop) {
             // final judge with the last update
             apply_op<double>(A, EPI_RESID_NORM, true, x64, this->y.p, ep);
-            vreduce(rwk[A.field][0], partial.p, 1, RED_NONE, 0, S.p, active.p, 0, 0.0, redout.p, s);
+            vreduce(work_set<double>(A.field).red, partial.p, 1, RED_NONE, 0, S.p, active.p, 0, 0.0, redout.p, s);
             outer_check(n, active.p, S.p, redout.p, s);
             HTS_HIP(hipEventRecord(e1, s));
             outer = get_active();
@@ -2172,6 +2190,7 @@ hts_status hts_apply_operator(hts_mesh *m, hts_field field, hts_precision prec, 
         HTS_HIP(hipSetDevice(m->desc.device));
         auto B = solo_batch(m);
         Batch &b = *B;
+        b.use_strips(true);
         std::vector<int32_t> all(1, 1);
         b.set_active(all);
         const bool steady = field == 0 && (dt <= 0.0 || m->B <= 0.0);
@@ -2196,7 +2215,7 @@ hts_status hts_apply_operator(hts_mesh *m, hts_field field, hts_precision prec, 
 
 // Time the fine-level operators of each mesh for several z-chunk depths
 // (the depth of node planes one workgroup marches through) and keep the
-// fastest per (degree, field, node dims).
+// fastest per (kernel family, field, precision, node dims).
 hts_status hts_autotune(hts_mesh *const *meshes, int32_t n)
 {
     return guard_call([&] {
@@ -2223,7 +2242,11 @@ hts_status hts_autotune(hts_mesh *const *meshes, int32_t n)
             HTS_HIP(hipEventCreate(&e0));
             HTS_HIP(hipEventCreate(&e1));
             HTS_HIP(hipEventCreate(&e2));
+            for (int kind = 0; kind < 2; kind++)
             for (int f = 0; f < 2; f++) {
+                const int fam = kernel_family(m, kind == 1);
+                if (kind == 1 && fam == kernel_family(m, false)) continue;
+                b.use_strips(kind == 1);
                 Tables &t = b.apply_tables(f, dt, f == 0 && m->B <= 0.0);
                 const int cands[] = {2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32, 48, 64};
                 double best[2] = {1e30, 1e30};
@@ -2232,11 +2255,11 @@ hts_status hts_autotune(hts_mesh *const *meshes, int32_t n)
                 for (int zc : cands) {
                     if (zc > m->N[2] && bz[0] > 0) break;
                     // Q2 depths are rounded up to whole cell layers
-                    const int eff = zc_for(m, f, 0, 1, zc);
+                    const int eff = zc_for(m, fam, f, 0, 1, zc);
                     if (std::find(tried.begin(), tried.end(), eff) != tried.end()) continue;
                     tried.push_back(eff);
                     b.zc_force[f][0] = b.zc_force[f][1] = zc;
-                    b.build_work();
+                    b.build_work(kind);
                     EpiArgs<double> e64{};
                     e64.b = b.inner_x.p;
                     EpiArgs<float> e32{};
@@ -2248,9 +2271,9 @@ hts_status hts_autotune(hts_mesh *const *meshes, int32_t n)
                     // each precision timed on its own (their kernels differ in
                     // registers and occupancy, so their best depths differ)
                     HTS_HIP(hipEventRecord(e0, b.s));
-                    for (int r = 0; r < 10; r++) b.apply_op<double>(t, EPI_RESID, true, b.inner_x.p, b.y.p, e64);
+                    for (int r = 0; r < 6; r++) b.apply_op<double>(t, EPI_RESID, true, b.inner_x.p, b.y.p, e64);
                     HTS_HIP(hipEventRecord(e1, b.s));
-                    for (int r = 0; r < 10; r++) b.apply_op<float>(t, EPI_RESID, true, b.x32.p, b.y32.p, e32);
+                    for (int r = 0; r < 6; r++) b.apply_op<float>(t, EPI_RESID, true, b.x32.p, b.y32.p, e32);
                     HTS_HIP(hipEventRecord(e2, b.s));
                     HTS_HIP(hipEventSynchronize(e2));
                     float ms[2] = {0.0f, 0.0f};
@@ -2258,9 +2281,11 @@ hts_status hts_autotune(hts_mesh *const *meshes, int32_t n)
                     HTS_HIP(hipEventElapsedTime(&ms[1], e1, e2));
                     static const bool verbose = env_or("HTS_VERBOSE", 0.0) > 0.0;
                     if (verbose)
-                        std::fprintf(stderr, "[hts] autotune q%d field %d %dx%dx%d z-depth %d: %d blocks, %.2f us FP64, "
-                                     "%.2f us FP32\n", m->p, f, m->N[0], m->N[1], m->N[2], zc, b.nwork[f][0],
-                                     100.0 * ms[0], 100.0 * ms[1]);
+                        std::fprintf(stderr, "[hts] autotune family %d field %d %dx%dx%d z-depth %d: %d blocks, %.2f us FP64, "
+                                     "%.2f us FP32\n", fam, f, m->N[0], m->N[1], m->N[2], zc, b.work_set<double>(f).n,
+                                     1000.0 / 6 * ms[0], 1000.0 / 6 * ms[1]);
+                    // deeper ones only get slower once both are well off their best
+                    if (ms[0] > 1.6 * best[0] && ms[1] > 1.6 * best[1]) break;
                     for (int pr = 0; pr < 2; pr++)
                         if (ms[pr] < best[pr]) {
                             best[pr] = ms[pr];
@@ -2269,7 +2294,7 @@ hts_status hts_autotune(hts_mesh *const *meshes, int32_t n)
                 }
                 b.zc_force[f][0] = b.zc_force[f][1] = 0;
                 for (int pr = 0; pr < 2; pr++)
-                    set_tuned_zc(kernel_degree(m), f, pr, m->N[0], m->N[1], m->N[2], bz[pr]);
+                    set_tuned_zc(fam, f, pr, m->N[0], m->N[1], m->N[2], bz[pr]);
             }
             (void)hipEventDestroy(e2);
             (void)hipEventDestroy(e0);
@@ -2288,6 +2313,7 @@ hts_status hts_solve_steady_pressure(hts_mesh *m, const hts_solver_opts *opts, h
         hts_solver_opts o = opts_or_default(opts);
         if (o.mode == HTS_MODE_LEARNED) o.mode = HTS_MODE_FP64;
         auto B = solo_batch(m);
+        B->use_strips(o.mode != HTS_MODE_FP32_REFINED);
         B->gather_state();
         FieldStats st = B->solve_pressure(0.0, true, o);
         if (stats) {
@@ -2314,6 +2340,7 @@ hts_status hts_solve_step(hts_mesh *m, double dt, const hts_solver_opts *opts, h
         HTS_HIP(hipSetDevice(m->desc.device));
         hts_solver_opts o = opts_or_default(opts);
         auto B = solo_batch(m);
+        B->use_strips(o.mode != HTS_MODE_FP32_REFINED);
         B->gather_state();
         std::vector<hts_step_stats> st;
         int rc = B->step(dt, o, &st);
@@ -2340,6 +2367,7 @@ hts_status hts_advance(hts_mesh *const *meshes, int32_t n, int32_t n_steps, doub
         HTS_HIP(hipSetDevice(ms[0]->desc.device));
         hts_solver_opts o = opts_or_default(opts);
         std::shared_ptr<Batch> B = n == 1 ? solo_batch(ms[0]) : multi_batch(ms);
+        B->use_strips(o.mode != HTS_MODE_FP32_REFINED);
         B->gather_state();
         std::vector<hts_step_stats> st;
         int rc = HTS_OK;
