@@ -35,6 +35,12 @@
 // slower on the large grid.  Waves side by side share a halo row; on their own
 // (four rows each) heat FP32 takes 80 us.
 //
+// One apply of one mesh (SOLO) takes its descriptor by value, finds its work from
+// the block index and reads the pressure state itself: 32^3 pressure FP32 8.5 ->
+// 5.0 us a call, 128 x 128 x 64 heat FP64 31.7 -> 18.6 (flag, slot and pressure
+// copies before it), 256 x 256 x 128 heat FP32 113 -> 69 (and no FP32 copy of the
+// pressure).
+//
 // Fused multiply-adds are written out and contraction is off, so that every
 // instance of the kernel (graded or not, each epilogue) rounds alike.
 //
@@ -216,8 +222,34 @@ __device__ __forceinline__ void line_cell(const OpDev &o, int b, int L, const T 
     }
 }
 
-template <typename T, int FIELD, int EPI, bool MASKED, bool GRADED>
-__global__ __launch_bounds__(64 * Q1S_WAVES) void k_q1_strip(const OpDev *__restrict__ ops, const WorkItem *__restrict__ work,
+// Where a launch finds its operator and work: in device tables (batches), or in
+// its own arguments (one mesh: two dependent reads less before a wave starts)
+struct Tabled {
+    const OpDev *ops;
+    const WorkItem *work;
+    __device__ __forceinline__ WorkItem item() const { return work[blockIdx.x]; }
+    __device__ __forceinline__ const OpDev &op(int inst) const { return ops[inst]; }
+};
+struct Solo {
+    OpDev o;
+    int32_t ntx, zc, total, per;   // work item i: tile i % ntx, planes from (i / ntx) zc; per = blocks of an XCD
+    __device__ __forceinline__ WorkItem item() const
+    {
+        const int i = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+        WorkItem w{};
+        w.inst = i < total ? 0 : -1;
+        w.tx = i % ntx;
+        w.z0 = i / ntx * zc;
+        w.z1 = min(o.NZ, w.z0 + zc);
+        return w;
+    }
+    __device__ __forceinline__ const OpDev &op(int) const { return o; }
+};
+
+// SOLO: descriptor and work in the arguments; its FP32 heat operator reads the
+// FP64 pressure state and forms the piezometric pressure as k_piezo32 does
+template <typename T, int FIELD, int EPI, bool MASKED, bool GRADED, bool SOLO>
+__global__ __launch_bounds__(64 * Q1S_WAVES) void k_q1_strip(const typename std::conditional<SOLO, Solo, Tabled>::type at,
                                                   const T *__restrict__ X, T *__restrict__ Y, EpiArgs<T> ep)
 {
     constexpr int R = Q1S_ROWS;                               // cell rows of a wave
@@ -225,9 +257,11 @@ __global__ __launch_bounds__(64 * Q1S_WAVES) void k_q1_strip(const OpDev *__rest
     __shared__ double red[Q1S_WAVES];
     __shared__ T xch[2][Q1S_WAVES][2][64];                    // upper-row sums of a wave's last cell row
 
-    const WorkItem wi = work[blockIdx.x];
-    if (ep.active && !ep.active[wi.inst]) return;
-    const OpDev &o = ops[wi.inst];
+    const WorkItem wi = at.item();
+    if (SOLO ? wi.inst < 0 : (ep.active && !ep.active[wi.inst])) return;
+    const OpDev &o = at.op(wi.inst);
+    constexpr bool PIEZO = SOLO && FIELD == 1 && sizeof(T) == 4;
+    using PT = typename std::conditional<PIEZO, double, T>::type;   // the pressure as stored
     const int nx = o.nx, ny = o.ny, nz = o.nz, NX = o.NX, NY = o.NY, NZ = o.NZ, m = o.dmask;
     constexpr bool CHEB = EPI == EPI_CHEB || EPI == EPI_CHEB0;
     constexpr bool HASB = EPI == EPI_RESID || EPI == EPI_RESID_NORM || CHEB;
@@ -236,7 +270,7 @@ __global__ __launch_bounds__(64 * Q1S_WAVES) void k_q1_strip(const OpDev *__rest
     const T *Bi = HASB ? ep.b + o.off : nullptr;
     T *Di = CHEB ? ep.d + o.off : nullptr;
     const T *Ii = CHEB ? ep.invd + o.off : nullptr;
-    const T *Pi = static_cast<const T *>(o.P);
+    const PT *Pi = static_cast<const PT *>(o.P);
     const T *kk = static_cast<const T *>(o.k), *lam = static_cast<const T *>(o.lam), *cT = static_cast<const T *>(o.cT);
     const int64_t plane = (int64_t)NX * NY, cplane = (int64_t)nx * ny;
     const uint32_t pbytes = (uint32_t)(plane * sizeof(T)), cbytes = (uint32_t)(cplane * sizeof(T));
@@ -298,7 +332,8 @@ __global__ __launch_bounds__(64 * Q1S_WAVES) void k_q1_strip(const OpDev *__rest
     const T fm = T(3.375 * o.q1m);
     const HaarStiff<T> fk(T(6.75 * o.q1x), T(6.75 * o.q1y), T(6.75 * o.q1z));
     const T vx = T(0.1875 * o.q1vx), vy = T(0.1875 * o.q1vy), vz = T(0.1875 * o.q1vz);
-    const T pz = T(4.0 * RSQRT3 * o.rho_g * o.hz);            // rho_g is 0 where the pressure is piezometric
+    const double rho_g = PIEZO ? 0.0 : o.rho_g;               // 0 where the pressure is piezometric
+    const T pz = T(4.0 * RSQRT3 * rho_g * o.hz);
     // graded meshes: parts of the cell column's hx, hy per row (times a factor
     // of the layer)
     const bool graded = GRADED && o.hzs != nullptr;
@@ -353,11 +388,24 @@ __global__ __launch_bounds__(64 * Q1S_WAVES) void k_q1_strip(const OpDev *__rest
             }
         }
     };
-    const uint32_t pb0 = xin ? nbase : OOB, pbr0 = xin && J0 >= 0 ? nbase : OOB;
-    auto load_p = [&](int k, T *u) {
-        const Rsrc rp = rsrc(Pi + k * plane, pbytes);
+    constexpr uint32_t PW = sizeof(PT) / sizeof(T);
+    const uint32_t pb0 = xin ? nbase * PW : OOB, pbr0 = xin && J0 >= 0 ? nbase * PW : OOB;
+    auto load_p = [&](int k, PT *u) {
+        const Rsrc rp = rsrc(Pi + k * plane, pbytes * PW);
 #pragma unroll
-        for (int r = 0; r <= R; r++) u[r] = bld<T>(rp, r == 0 ? pbr0 : pb0 + r * rowb);
+        for (int r = 0; r <= R; r++) u[r] = bld<PT>(rp, r == 0 ? pbr0 : pb0 + r * rowb * PW);
+    };
+    const double pref = PIEZO && o.cadv != 0.0 ? (double)Pi[0] : 0.0;
+    // loaded pressure of plane k -> the operator's
+    auto use_p = [&](int k, const PT *u, T *p) {
+        if (PIEZO) {
+            const double zk = graded ? o.zn[k] - o.zn[0] : k * o.hz;
+#pragma unroll
+            for (int r = 0; r <= R; r++) p[r] = T(fma_(o.rho_g, zk, (double)u[r] - pref));
+        } else {
+#pragma unroll
+            for (int r = 0; r <= R; r++) p[r] = T(u[r]);
+        }
     };
     auto load_c = [&](int L, T *ck, T *cl, T *cc) {
         const Rsrc rk = rsrc(kk + L * cplane, cbytes);
@@ -432,21 +480,24 @@ __global__ __launch_bounds__(64 * Q1S_WAVES) void k_q1_strip(const OpDev *__rest
         for (int q = 0; q < R; q++) tc[q] = T(0);
         load_x(La, lo);
         load_x(La + 1, up);
-        if (ADV) { load_p(La, pl); load_p(La + 1, pu); }
+        PT pa[ADV ? R + 1 : 1], pb[ADV ? R + 1 : 1];
+        if (ADV) { load_p(La, pa); load_p(La + 1, pb); }
         load_c(La, ck, cl, cc);
         mask_cols(La, lo);
         T xl[ADV ? R + 1 : 1];                                // x differences of the lower plane's pressure
         if (ADV) {
+            use_p(La, pa, pl);
 #pragma unroll
             for (int r = 0; r <= R; r++) xl[ADV ? r : 0] = pl[ADV ? r : 0] - from_right(pl[ADV ? r : 0]);
         }
         for (int L = La; L <= Lb; L++) {
-            T xn[R + 1], pn[ADV ? R + 1 : 1], kn[R], ln[R], cn[R];
+            T xn[R + 1], kn[R], ln[R], cn[R];
+            if (ADV) use_p(L + 1, pb, pu);
             // loads of this layer's epilogue, then of the next layer
             if (L >= kb) load_e(L);
             if (L < Lb) {
                 load_x(L + 2, xn);
-                if (ADV) load_p(L + 2, pn);
+                if (ADV) load_p(L + 2, pb);
                 load_c(L + 1, kn, ln, cn);
             }
             mask_cols(L + 1, up);
@@ -459,7 +510,7 @@ __global__ __launch_bounds__(64 * Q1S_WAVES) void k_q1_strip(const OpDev *__rest
                 uz = T(o.cs * ihz * 0.1875);
                 uv = T(-o.cadv * (0.1875 * 0.125) * hz);
                 uw = T(-o.cadv * (0.1875 * 0.125) * ihz);
-                g = T(4.0 * RSQRT3 * o.rho_g * hz);
+                g = T(4.0 * RSQRT3 * rho_g * hz);
             }
             T v[R];
             T zs0 = lo[0] + up[0], zd0 = (lo[0] - up[0]) * r3;
@@ -529,10 +580,7 @@ __global__ __launch_bounds__(64 * Q1S_WAVES) void k_q1_strip(const OpDev *__rest
             for (int r = 0; r <= R; r++) {
                 lo[r] = up[r];
                 up[r] = xn[r];
-                if (ADV) {
-                    pl[ADV ? r : 0] = pu[ADV ? r : 0];
-                    pu[ADV ? r : 0] = pn[ADV ? r : 0];
-                }
+                if (ADV) pl[ADV ? r : 0] = pu[ADV ? r : 0];
                 if (r < R) { ck[r] = kn[r]; cl[r] = ln[r]; cc[r] = cn[r]; }
             }
         }
@@ -564,7 +612,8 @@ template <typename T, int FIELD, int EPI, bool MASKED, bool G>
 static void launch_k(int nwork, const OpDev *ops, const WorkItem *work, const T *x, T *y, const EpiArgs<T> &ep,
                      hipStream_t s)
 {
-    k_q1_strip<T, FIELD, EPI, MASKED, G><<<dim3(nwork), dim3(64 * Q1S_WAVES), 0, s>>>(ops, work, x, y, ep);
+    k_q1_strip<T, FIELD, EPI, MASKED, G, false><<<dim3(nwork), dim3(64 * Q1S_WAVES), 0, s>>>(Tabled{ops, work}, x, y,
+                                                                                           ep);
 }
 
 template <typename T, int FIELD, bool MASKED, bool G>
@@ -614,5 +663,24 @@ template void launch_q1s<double>(int, int, bool, bool, const OpDev *, const Work
                                 double *, const EpiArgs<double> &, hipStream_t);
 template void launch_q1s<float>(int, int, bool, bool, const OpDev *, const WorkItem *, int, const float *,
                                float *, const EpiArgs<float> &, hipStream_t);
+
+// y = A x (masked) of one mesh: op by value (off 0), the heat operator's P the FP64
+// pressure state, tiles of ntx blocks and planes of zc
+template <typename T>
+void launch_q1s_solo(int field, bool graded, const OpDev &op, int ntx, int zc, const T *x, T *y, hipStream_t s)
+{
+    Solo a{op, ntx, zc, 0, 0};
+    a.total = ntx * ((op.NZ + zc - 1) / zc);
+    a.per = (a.total + 7) / 8;
+    const dim3 grid((unsigned)(8 * a.per)), block(64 * Q1S_WAVES);
+    EpiArgs<T> ep{};
+    if (field == 0 && !graded) k_q1_strip<T, 0, EPI_STORE, true, false, true><<<grid, block, 0, s>>>(a, x, y, ep);
+    else if (field == 0) k_q1_strip<T, 0, EPI_STORE, true, true, true><<<grid, block, 0, s>>>(a, x, y, ep);
+    else if (!graded) k_q1_strip<T, 1, EPI_STORE, true, false, true><<<grid, block, 0, s>>>(a, x, y, ep);
+    else k_q1_strip<T, 1, EPI_STORE, true, true, true><<<grid, block, 0, s>>>(a, x, y, ep);
+    HTS_LAUNCH_CHECK();
+}
+template void launch_q1s_solo<double>(int, bool, const OpDev &, int, int, const double *, double *, hipStream_t);
+template void launch_q1s_solo<float>(int, bool, const OpDev &, int, int, const float *, float *, hipStream_t);
 
 }  // namespace hts

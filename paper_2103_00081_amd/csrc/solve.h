@@ -15,6 +15,8 @@ namespace hts {
 template <typename T>
 void launch_apply(int family, int field, int epi, bool masked, bool graded, const OpDev *ops, const WorkItem *work,
                   int nwork, const T *x, T *y, const EpiArgs<T> &ep, hipStream_t s);
+template <typename T>
+void launch_q1s_solo(int field, bool graded, const OpDev &op, int ntx, int zc, const T *x, T *y, hipStream_t s);
 void launch_inv_diag(const OpDev &op, double *inv_diag, hipStream_t s);
 void launch_q1_stencil(const OpDev &op, double *S, hipStream_t s);
 void launch_fine_stencil(const OpDev &op, double *S, hipStream_t s);
@@ -216,6 +218,7 @@ struct Batch {
     bool any_active();
     VecCtx vctx(bool use_active = true) const;
 
+    void timed_apply(int field, int epi, int prec, const std::function<void()> &launch);
     template <typename T>
     void fine_apply(int field, const OpDev *ops, int epi, bool masked, const T *x, T *y, const EpiArgs<T> &ep);
     template <typename T> void apply_lvl(Hier &H, int l, int epi, bool masked, const T *x, T *y, EpiArgs<T> ep);

@@ -546,25 +546,34 @@ static double apply_flops(int field, int p, int64_t cells)
     return (p == 1 ? q1 : 8.0 * q1) * (double)cells;
 }
 
-template <typename T>
-void Batch::fine_apply(int field, const OpDev *ops, int epi, bool masked, const T *x, T *y, const EpiArgs<T> &ep)
+// a fine-level operator launch, between two events while timing is on
+void Batch::timed_apply(int field, int epi, int prec, const std::function<void()> &launch)
 {
-    const WorkSet &W = work_set<T>(field);
     if (!g_timing.on) {
-        launch_apply<T>(family(), field, epi, masked, graded, ops, W.work.p, W.n, x, y, ep, s);
+        launch();
         return;
     }
+    const size_t ts = prec ? sizeof(float) : sizeof(double);
     TimingRec r{};
     r.a = g_timing.get();
     r.b = g_timing.get();
     r.field = field;
-    r.prec = std::is_same<T, double>::value ? 0 : 1;
-    r.bytes = apply_bytes(field, epi, ntot, ctot, sizeof(T));
+    r.prec = prec;
+    r.bytes = apply_bytes(field, epi, ntot, ctot, (int)ts);
     r.flops = apply_flops(field, p, ctot);
     HTS_HIP(hipEventRecord(r.a, s));
-    launch_apply<T>(family(), field, epi, masked, graded, ops, W.work.p, W.n, x, y, ep, s);
+    launch();
     HTS_HIP(hipEventRecord(r.b, s));
     g_timing.recs.push_back(r);
+}
+
+template <typename T>
+void Batch::fine_apply(int field, const OpDev *ops, int epi, bool masked, const T *x, T *y, const EpiArgs<T> &ep)
+{
+    const WorkSet &W = work_set<T>(field);
+    timed_apply(field, epi, sizeof(T) == 4, [&] {
+        launch_apply<T>(family(), field, epi, masked, graded, ops, W.work.p, W.n, x, y, ep, s);
+    });
 }
 
 template <typename T>
@@ -2191,19 +2200,37 @@ hts_status hts_apply_operator(hts_mesh *m, hts_field field, hts_precision prec, 
         auto B = solo_batch(m);
         Batch &b = *B;
         b.use_strips(true);
+        const bool steady = field == 0 && (dt <= 0.0 || m->B <= 0.0);
+        const bool fp32 = prec == HTS_FP32;
+        if (field == 1 && b.nlsrc > 0) {
+            std::vector<double> tn(1, m->t + dt), fs(1, dt);
+            b.set_time(tn, fs);
+            launch_source_values(b.lsrc.p, b.nlsrc, b.S.p, b.lcoef.p, b.s);
+        }
+        if (b.family() == Q1_STRIP) {
+            // one launch: the descriptor goes by value and the heat operator
+            // reads the mesh's own pressure state
+            OpDev o = make_op(m, field, fp32, dt, steady, false);
+            o.P = m->P.p;
+            o.lcoef = b.lcoef.p;
+            int ntx, nty;
+            tile_grid(m, Q1_STRIP, field, ntx, nty);
+            const int zc = zc_for(m, Q1_STRIP, field, fp32, ntx, 0);
+            b.timed_apply(field, EPI_STORE, fp32, [&] {
+                if (fp32) launch_q1s_solo<float>(field, m->graded, o, ntx, zc, (const float *)x_dev, (float *)y_dev, b.s);
+                else launch_q1s_solo<double>(field, m->graded, o, ntx, zc, (const double *)x_dev, (double *)y_dev, b.s);
+            });
+            return;
+        }
         std::vector<int32_t> all(1, 1);
         b.set_active(all);
-        const bool steady = field == 0 && (dt <= 0.0 || m->B <= 0.0);
         Tables &t = b.apply_tables(field, dt, steady);
         if (field == 1) {
             HTS_HIP(hipMemcpyAsync(b.P1.p, m->P.p, m->nnode * sizeof(double), hipMemcpyDeviceToDevice, b.s));
             VecCtx v = b.vctx(false);
             vpiezo32(v, b.massH.d64.p, b.P1.p, b.P32.p);
-            std::vector<double> tn(1, m->t + dt), fs(1, dt);
-            b.set_time(tn, fs);
-            launch_source_values(b.lsrc.p, b.nlsrc, b.S.p, b.lcoef.p, b.s);
         }
-        if (prec == HTS_FP64) {
+        if (!fp32) {
             EpiArgs<double> ep{};
             b.apply_op<double>(t, EPI_STORE, true, (const double *)x_dev, (double *)y_dev, ep);
         } else {
