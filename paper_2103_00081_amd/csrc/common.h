@@ -178,7 +178,7 @@ struct LevelGeo {              // one instance on one multigrid level
 // ------------------------------------------------------------ launchers
 // Operator kernel families: the LDS tile kernels by degree (op_q1.hip,
 // op_q2.hip), those of general hexahedra (op_hex.hip, node coordinates in
-// OpDev::xyz), and the strip kernels of box meshes (op_q1s.hip)
+// OpDev::xyz), and the strip kernels of box meshes (op_q1s.hip, op_q2s.hip)
 constexpr int DEGREE_HEX = 3;
 constexpr int Q1_STRIP = 4;
 // Q1 strips: waves per block (side by side along y), owned node columns per
@@ -186,6 +186,11 @@ constexpr int Q1_STRIP = 4;
 constexpr int Q1S_WAVES = 4;
 constexpr int Q1S_OWNED = 62;
 constexpr int Q1S_ROWS = 2;
+// Q2 strips: waves per block (one cell row each; the FP64 heat kernel's 340 registers
+// allow one wave per SIMD) and owned cell columns per block
+constexpr int Q2_STRIP = 5;
+constexpr int q2s_waves(int field, bool fp64) { return field == 1 && fp64 ? 4 : 8; }
+constexpr int Q2S_OWNED = 62;
 template <typename T>
 void launch_apply(int family, int field, int epi, bool masked, bool graded, const OpDev *ops, const WorkItem *work,
                   int nwork, const T *x, T *y, const EpiArgs<T> &ep, hipStream_t s);

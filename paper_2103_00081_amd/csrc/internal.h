@@ -222,10 +222,16 @@ OpDev make_op(const hts_mesh *m, int field, bool fp32, double dt, bool steady, b
 inline int kernel_family(const hts_mesh *m, bool strips)
 {
     if (m->general) return DEGREE_HEX;
-    return strips && m->p == 1 ? Q1_STRIP : m->p;
+    if (!strips) return m->p;
+    return m->p == 1 ? Q1_STRIP : Q2_STRIP;
 }
 // tiles per node plane of a kernel family along x and y
-void tile_grid(const hts_mesh *m, int family, int field, int &ntx, int &nty);
+void tile_grid(const hts_mesh *m, int family, int field, bool fp64, int &ntx, int &nty);
+// y = A x (masked, distinct buffers) of one mesh by its strip kernel, one launch:
+// op by value with off 0 (heat: P the FP64 pressure state also for FP32), planes of
+// zc per block
+template <typename T>
+void launch_strip_solo(const hts_mesh *m, int field, const OpDev &op, int zc, const T *x, T *y, hipStream_t s);
 // node planes per work item of the operator kernels (force > 0: that depth)
 int zc_for(const hts_mesh *M, int family, int field, int prec, int64_t tiles, int force);
 

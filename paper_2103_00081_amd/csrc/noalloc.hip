@@ -118,9 +118,11 @@ extern "C" hts_status hts_apply_operator_noalloc(hts_mesh *m, hts_field field, h
         const hipStream_t s = m->stream;
         const bool fp32 = prec == HTS_FP32;
         const bool steady = field == 0 && (dt <= 0.0 || m->B <= 0.0);
-        const int family = kernel_family(m, true);
+        // the scratch holds the work list and descriptors of the tile kernels (the
+        // strip kernels of box meshes need neither; the limit is the same)
+        const int family = kernel_family(m, false);
         int ntx, nty;
-        tile_grid(m, family, field, ntx, nty);
+        tile_grid(m, family, field, !fp32, ntx, nty);
         const int zc = zc_for(m, family, field, fp32 ? 1 : 0, (int64_t)ntx * nty, 0);
         const int64_t nzc = (m->N[2] + zc - 1) / zc;
         const int64_t nwork = (int64_t)ntx * nty * nzc;
@@ -149,6 +151,35 @@ extern "C" hts_status hts_apply_operator_noalloc(hts_mesh *m, hts_field field, h
         Chunk *chunks = reinterpret_cast<Chunk *>(base + o_chunk);
         float *P32 = reinterpret_cast<float *>(base + o_p32);
 
+        if (field == 1) {
+            // time slots of instance 0, then the line-source coefficients at t + dt
+            double hS[NSLOT];
+            for (int i = 0; i < NSLOT; i++) hS[i] = 0.0;
+            hS[S_TNEW] = m->t + dt;
+            hS[S_FSCALE] = dt;
+            put(base + o_S, hS, sizeof(hS), s);
+            if (nsrc > 0) {
+                std::vector<SrcDev> ls(m->line_srcs);
+                for (SrcDev &sd : ls) sd.inst = 0;
+                put(base + o_src, ls.data(), ls.size() * sizeof(SrcDev), s);
+                launch_source_values(srcs, nsrc, S, coef, s);
+            }
+        }
+        if (family != DEGREE_HEX) {
+            // box meshes: one launch of the strip kernel, as hts_apply_operator
+            const int strip = kernel_family(m, true);
+            int sx, sy;
+            tile_grid(m, strip, field, !fp32, sx, sy);
+            const int szc = zc_for(m, strip, field, fp32 ? 1 : 0, (int64_t)sx * sy, 0);
+            OpDev op = make_op(m, field, fp32, dt, steady, false);
+            op.P = m->P.p;
+            op.lcoef = coef;
+            if (fp32) launch_strip_solo<float>(m, field, op, szc, static_cast<const float *>(x_dev),
+                                               static_cast<float *>(y_dev), s);
+            else launch_strip_solo<double>(m, field, op, szc, static_cast<const double *>(x_dev),
+                                           static_cast<double *>(y_dev), s);
+            return;
+        }
         // descriptors: [0] FP64, [1] FP32, as the solo batch builds them
         OpDev h[2];
         for (int q = 0; q < 2; q++) {
@@ -164,26 +195,12 @@ extern "C" hts_status hts_apply_operator_noalloc(hts_mesh *m, hts_field field, h
         k_make_work<<<dim3((unsigned)((nwork + 255) / 256)), dim3(256), 0, s>>>(work, ntx, nty, zc, m->N[2],
                                                                                (int)nwork);
         HTS_LAUNCH_CHECK();
-        if (field == 1) {
-            // time slots of instance 0, then the line-source coefficients at t + dt
-            double hS[NSLOT];
-            for (int i = 0; i < NSLOT; i++) hS[i] = 0.0;
-            hS[S_TNEW] = m->t + dt;
-            hS[S_FSCALE] = dt;
-            put(base + o_S, hS, sizeof(hS), s);
-            if (nsrc > 0) {
-                std::vector<SrcDev> ls(m->line_srcs);
-                for (SrcDev &sd : ls) sd.inst = 0;
-                put(base + o_src, ls.data(), ls.size() * sizeof(SrcDev), s);
-                launch_source_values(srcs, nsrc, S, coef, s);
-            }
-            if (nchunk) {
-                k_make_chunks<<<dim3((unsigned)((nchunk + 255) / 256)), dim3(256), 0, s>>>(chunks, m->nnode, clen,
-                                                                                         (int)nchunk);
-                HTS_LAUNCH_CHECK();
-                VecCtx v{chunks, (int)nchunk, nullptr, S, s};
-                vpiezo32(v, ops, m->P.p, P32);
-            }
+        if (nchunk) {
+            k_make_chunks<<<dim3((unsigned)((nchunk + 255) / 256)), dim3(256), 0, s>>>(chunks, m->nnode, clen,
+                                                                                     (int)nchunk);
+            HTS_LAUNCH_CHECK();
+            VecCtx v{chunks, (int)nchunk, nullptr, S, s};
+            vpiezo32(v, ops, m->P.p, P32);
         }
         if (!fp32) {
             EpiArgs<double> ep{};

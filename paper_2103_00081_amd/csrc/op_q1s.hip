@@ -50,60 +50,14 @@
 // drops, so the march needs no selects or branches for them.
 #include <type_traits>
 
-#include "common.h"
-#include "dev_util.h"
+#include "strip.h"
 
 namespace hts {
 
 namespace {
 
-// ----------------------------------------------- raw buffer access, lane shifts
-constexpr uint32_t OOB = 0xFF000000u;   // byte offset past any plane (planes stay below 2^31 bytes)
-
-using Rsrc = __amdgpu_buffer_rsrc_t;
-// `bytes` bytes from p; 0: every access is out of range (loads give zero)
-__device__ __forceinline__ static Rsrc rsrc(const void *p, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
-}
-template <typename T>
-__device__ __forceinline__ static T bld(Rsrc r, uint32_t off)
-{
-    if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
-    else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
-}
-template <typename T>
-__device__ __forceinline__ static void bst(Rsrc r, uint32_t off, T v)
-{
-    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-    if constexpr (sizeof(T) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0, 0);
-    else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, off, 0, 0);
-}
-
-// the value of lane + 1 (wave_shl:1) and of lane - 1 (wave_shr:1); zero past
-// the ends.  All 64 lanes are active where these are used.
-template <int CTRL>
-__device__ __forceinline__ static float wshift(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ static double wshift(double v)
-{
-    struct P { int lo, hi; } p = __builtin_bit_cast(P, v);
-    p.lo = __builtin_amdgcn_update_dpp(0, p.lo, CTRL, 0xf, 0xf, true);
-    p.hi = __builtin_amdgcn_update_dpp(0, p.hi, CTRL, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, p);
-}
-template <typename T>
-__device__ __forceinline__ static T from_right(T v) { return wshift<0x130>(v); }
-template <typename T>
-__device__ __forceinline__ static T from_left(T v) { return wshift<0x138>(v); }
-
 constexpr double RSQRT3 = 0.57735026918962576451;
 #pragma clang fp contract(off)
-__device__ __forceinline__ static float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ static double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 // o += the Gauss-point product of A and v projected back (2D scaled Haar
 // coordinates: 0 ss, 1 ds, 2 sd, 3 dd)
@@ -221,30 +175,6 @@ __device__ __forceinline__ void line_cell(const OpDev &o, int b, int L, const T 
         b = e->next;
     }
 }
-
-// Where a launch finds its operator and work: in device tables (batches), or in
-// its own arguments (one mesh: two dependent reads less before a wave starts)
-struct Tabled {
-    const OpDev *ops;
-    const WorkItem *work;
-    __device__ __forceinline__ WorkItem item() const { return work[blockIdx.x]; }
-    __device__ __forceinline__ const OpDev &op(int inst) const { return ops[inst]; }
-};
-struct Solo {
-    OpDev o;
-    int32_t ntx, zc, total, per;   // work item i: tile i % ntx, planes from (i / ntx) zc; per = blocks of an XCD
-    __device__ __forceinline__ WorkItem item() const
-    {
-        const int i = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-        WorkItem w{};
-        w.inst = i < total ? 0 : -1;
-        w.tx = i % ntx;
-        w.z0 = i / ntx * zc;
-        w.z1 = min(o.NZ, w.z0 + zc);
-        return w;
-    }
-    __device__ __forceinline__ const OpDev &op(int) const { return o; }
-};
 
 // SOLO: descriptor and work in the arguments; its FP32 heat operator reads the
 // FP64 pressure state and forms the piezometric pressure as k_piezo32 does
@@ -634,44 +564,37 @@ static void dispatch_epi(int epi, const OpDev *ops, const WorkItem *work, int nw
     }
 }
 
-template <typename T, bool G>
+template <bool G>
 static void launch_q1s_g(int field, int epi, bool masked, const OpDev *ops, const WorkItem *work, int nwork,
-                        const T *x, T *y, const EpiArgs<T> &ep, hipStream_t s)
+                         const double *x, double *y, const EpiArgs<double> &ep, hipStream_t s)
 {
     if (field == 0) {
-        if (masked) dispatch_epi<T, 0, true, G>(epi, ops, work, nwork, x, y, ep, s);
-        else dispatch_epi<T, 0, false, G>(epi, ops, work, nwork, x, y, ep, s);
+        if (masked) dispatch_epi<double, 0, true, G>(epi, ops, work, nwork, x, y, ep, s);
+        else dispatch_epi<double, 0, false, G>(epi, ops, work, nwork, x, y, ep, s);
     } else {
-        if (masked) dispatch_epi<T, 1, true, G>(epi, ops, work, nwork, x, y, ep, s);
-        else dispatch_epi<T, 1, false, G>(epi, ops, work, nwork, x, y, ep, s);
+        if (masked) dispatch_epi<double, 1, true, G>(epi, ops, work, nwork, x, y, ep, s);
+        else dispatch_epi<double, 1, false, G>(epi, ops, work, nwork, x, y, ep, s);
     }
 }
 
-// graded: some instance has a graded mesh; those kernels form the per-cell
-// factors per layer, the uniform ones keep them in registers
-template <typename T>
+// FP64 only: the solvers' FP32 operators are those of the refined mode, which keeps
+// the tile kernels.  graded: some instance has a graded mesh; those kernels form
+// the per-cell factors per layer, the uniform ones keep them in registers
 void launch_q1s(int field, int epi, bool masked, bool graded, const OpDev *ops, const WorkItem *work, int nwork,
-               const T *x, T *y, const EpiArgs<T> &ep, hipStream_t s)
+                const double *x, double *y, const EpiArgs<double> &ep, hipStream_t s)
 {
     if (nwork <= 0) return;
-    if (graded) launch_q1s_g<T, true>(field, epi, masked, ops, work, nwork, x, y, ep, s);
-    else launch_q1s_g<T, false>(field, epi, masked, ops, work, nwork, x, y, ep, s);
+    if (graded) launch_q1s_g<true>(field, epi, masked, ops, work, nwork, x, y, ep, s);
+    else launch_q1s_g<false>(field, epi, masked, ops, work, nwork, x, y, ep, s);
     HTS_LAUNCH_CHECK();
 }
-
-template void launch_q1s<double>(int, int, bool, bool, const OpDev *, const WorkItem *, int, const double *,
-                                double *, const EpiArgs<double> &, hipStream_t);
-template void launch_q1s<float>(int, int, bool, bool, const OpDev *, const WorkItem *, int, const float *,
-                               float *, const EpiArgs<float> &, hipStream_t);
 
 // y = A x (masked) of one mesh: op by value (off 0), the heat operator's P the FP64
 // pressure state, tiles of ntx blocks and planes of zc
 template <typename T>
 void launch_q1s_solo(int field, bool graded, const OpDev &op, int ntx, int zc, const T *x, T *y, hipStream_t s)
 {
-    Solo a{op, ntx, zc, 0, 0};
-    a.total = ntx * ((op.NZ + zc - 1) / zc);
-    a.per = (a.total + 7) / 8;
+    const Solo a = solo_work(op, ntx, zc);
     const dim3 grid((unsigned)(8 * a.per)), block(64 * Q1S_WAVES);
     EpiArgs<T> ep{};
     if (field == 0 && !graded) k_q1_strip<T, 0, EPI_STORE, true, false, true><<<grid, block, 0, s>>>(a, x, y, ep);

@@ -15,8 +15,6 @@ namespace hts {
 template <typename T>
 void launch_apply(int family, int field, int epi, bool masked, bool graded, const OpDev *ops, const WorkItem *work,
                   int nwork, const T *x, T *y, const EpiArgs<T> &ep, hipStream_t s);
-template <typename T>
-void launch_q1s_solo(int field, bool graded, const OpDev &op, int ntx, int zc, const T *x, T *y, hipStream_t s);
 void launch_inv_diag(const OpDev &op, double *inv_diag, hipStream_t s);
 void launch_q1_stencil(const OpDev &op, double *S, hipStream_t s);
 void launch_fine_stencil(const OpDev &op, double *S, hipStream_t s);

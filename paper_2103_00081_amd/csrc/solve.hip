@@ -180,10 +180,11 @@ int tuned_zc(int family, int field, int prec, int NX, int NY, int NZ)
     return it == g_tune.end() ? 0 : it->second;
 }
 
-// Q1 strips: Q1S_OWNED of the node columns of the y bands laid end to end (one
-// empty column after each band).  Tiles: Q1 wide for the pressure operator and
+// Strips: Q1S_OWNED of the node columns of the y bands laid end to end (one empty
+// column after each band), Q2S_OWNED of the cell columns (two more per band).
+// Tiles: Q1 wide for the pressure operator and
 // narrow for the heat operator and general hexahedra, Q2 30 x 30.
-void tile_grid(const hts_mesh *m, int family, int field, int &ntx, int &nty)
+void tile_grid(const hts_mesh *m, int family, int field, bool fp64, int &ntx, int &nty)
 {
     if (family == Q1_STRIP) {
         const int own = Q1S_WAVES * Q1S_ROWS - 1;
@@ -192,9 +193,38 @@ void tile_grid(const hts_mesh *m, int family, int field, int &ntx, int &nty)
         nty = 1;
         return;
     }
+    if (family == Q2_STRIP) {
+        const int own = 2 * (q2s_waves(field, fp64) - 1);
+        const int64_t cols = (int64_t)((m->N[1] + own - 1) / own) * (m->n[0] + 2);
+        ntx = (int)((cols + Q2S_OWNED - 1) / Q2S_OWNED);
+        nty = 1;
+        return;
+    }
     const int ox = family == 2 ? 30 : (field == 0 && family == 1 ? 31 : 15), oy = family == 2 ? 30 : 15;
     ntx = (m->N[0] + ox - 1) / ox;
     nty = (m->N[1] + oy - 1) / oy;
+}
+
+// Q2 strips: a block holds a CU (FP32 pressure: half of one) for one cell layer per
+// 3 us (pressure) or 6 us (heat), whatever its neighbours do, and a march of L layers
+// takes about L + 2 of them (one repeated layer, first loads), so the depth with the
+// fewest such steps over all rounds of blocks.  128 x 128 x 64: FP64 pressure 54.1 us
+// at its depth 22 (240 blocks), 59 to 70 at 12, 16 and 26; FP32 heat 79.3 at 22, 92 to
+// 117; FP32 pressure 39.4 at 12, 43 to 50 at 8, 16 and 26; FP64 heat 161 at 26, 162 at
+// 12, 170 to 203 at 10, 16 and 34.
+static int q2_strip_depth(int64_t tiles, int NZ, int field, int prec)
+{
+    const int64_t room = field == 0 && prec == 1 ? 512 : 256;
+    int best = 2;
+    int64_t cost = INT64_MAX;
+    for (int zc = 2; zc < NZ + 2; zc += 2) {
+        const int64_t rounds = (tiles * ((NZ + zc - 1) / zc) + room - 1) / room, c = rounds * (zc / 2 + 2);
+        if (c <= cost) {
+            cost = c;
+            best = zc;
+        }
+    }
+    return best;
 }
 
 int zc_for(const hts_mesh *M, int family, int field, int prec, int64_t tiles, int force)
@@ -205,6 +235,7 @@ int zc_for(const hts_mesh *M, int family, int field, int prec, int64_t tiles, in
     if (force > 0) return fit(force);
     const int t = tuned_zc(family, field, prec, M->N[0], M->N[1], NZ);
     if (t > 0) return fit(t);
+    if (family == Q2_STRIP) return fit(q2_strip_depth(tiles, NZ, field, prec));
     if (family == Q1_STRIP) {
         // about 1000 blocks, four for each CU.  Small grids: the shortest
         // march (48^3 heat FP32: 9.5 us at depth 2, 13 at 4); large ones: at
@@ -231,7 +262,7 @@ void Batch::build_work(int kind)
             hts_mesh *M = m[i];
             const int fam = kernel_family(M, kind == 1);
             int tx, ty;
-            tile_grid(M, fam, f, tx, ty);
+            tile_grid(M, fam, f, pr == 0, tx, ty);
             const int zc = zc_for(M, fam, f, pr, (int64_t)tx * ty, zc_force[f][pr]);
             for (int z0 = 0; z0 < M->N[2]; z0 += zc)
                 for (int y = 0; y < ty; y++)
@@ -2207,18 +2238,18 @@ hts_status hts_apply_operator(hts_mesh *m, hts_field field, hts_precision prec, 
             b.set_time(tn, fs);
             launch_source_values(b.lsrc.p, b.nlsrc, b.S.p, b.lcoef.p, b.s);
         }
-        if (b.family() == Q1_STRIP) {
+        if (b.strips) {
             // one launch: the descriptor goes by value and the heat operator
             // reads the mesh's own pressure state
             OpDev o = make_op(m, field, fp32, dt, steady, false);
             o.P = m->P.p;
             o.lcoef = b.lcoef.p;
             int ntx, nty;
-            tile_grid(m, Q1_STRIP, field, ntx, nty);
-            const int zc = zc_for(m, Q1_STRIP, field, fp32, ntx, 0);
+            tile_grid(m, b.family(), field, !fp32, ntx, nty);
+            const int zc = zc_for(m, b.family(), field, fp32, (int64_t)ntx * nty, 0);
             b.timed_apply(field, EPI_STORE, fp32, [&] {
-                if (fp32) launch_q1s_solo<float>(field, m->graded, o, ntx, zc, (const float *)x_dev, (float *)y_dev, b.s);
-                else launch_q1s_solo<double>(field, m->graded, o, ntx, zc, (const double *)x_dev, (double *)y_dev, b.s);
+                if (fp32) launch_strip_solo<float>(m, field, o, zc, (const float *)x_dev, (float *)y_dev, b.s);
+                else launch_strip_solo<double>(m, field, o, zc, (const double *)x_dev, (double *)y_dev, b.s);
             });
             return;
         }
@@ -2273,9 +2304,17 @@ hts_status hts_autotune(hts_mesh *const *meshes, int32_t n)
             for (int f = 0; f < 2; f++) {
                 const int fam = kernel_family(m, kind == 1);
                 if (kind == 1 && fam == kernel_family(m, false)) continue;
-                b.use_strips(kind == 1);
+                b.use_strips(false);
+                OpDev o64 = make_op(m, f, false, dt, f == 0 && m->B <= 0.0, false), o32 = make_op(m, f, true, dt, f == 0 && m->B <= 0.0, false);
+                o64.P = o32.P = m->P.p;
+                o64.lcoef = o32.lcoef = b.lcoef.p;
                 Tables &t = b.apply_tables(f, dt, f == 0 && m->B <= 0.0);
-                const int cands[] = {2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32, 48, 64};
+                std::vector<int> cands = {2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32, 48, 64};
+                for (int pr = 0; fam == Q2_STRIP && pr < 2; pr++) {
+                    int tx, ty;
+                    tile_grid(m, fam, f, pr == 0, tx, ty);
+                    cands.insert(cands.begin(), q2_strip_depth((int64_t)tx * ty, m->N[2], f, pr));
+                }
                 double best[2] = {1e30, 1e30};
                 int bz[2] = {0, 0};
                 std::vector<int> tried;
@@ -2285,22 +2324,30 @@ hts_status hts_autotune(hts_mesh *const *meshes, int32_t n)
                     const int eff = zc_for(m, fam, f, 0, 1, zc);
                     if (std::find(tried.begin(), tried.end(), eff) != tried.end()) continue;
                     tried.push_back(eff);
-                    b.zc_force[f][0] = b.zc_force[f][1] = zc;
-                    b.build_work(kind);
-                    EpiArgs<double> e64{};
-                    e64.b = b.inner_x.p;
-                    EpiArgs<float> e32{};
-                    e32.b = b.x32.p;
+                    std::function<void()> run64, run32;
+                    if (kind == 1) {
+                        run64 = [&] { launch_strip_solo<double>(m, f, o64, eff, b.inner_x.p, b.y.p, b.s); };
+                        run32 = [&] { launch_strip_solo<float>(m, f, o32, eff, b.x32.p, b.y32.p, b.s); };
+                    } else {
+                        b.zc_force[f][0] = b.zc_force[f][1] = zc;
+                        b.build_work(0);
+                        EpiArgs<double> e64{};
+                        e64.b = b.inner_x.p;
+                        EpiArgs<float> e32{};
+                        e32.b = b.x32.p;
+                        run64 = [&, e64] { b.apply_op<double>(t, EPI_RESID, true, b.inner_x.p, b.y.p, e64); };
+                        run32 = [&, e32] { b.apply_op<float>(t, EPI_RESID, true, b.x32.p, b.y32.p, e32); };
+                    }
                     for (int w = 0; w < 2; w++) {
-                        b.apply_op<double>(t, EPI_RESID, true, b.inner_x.p, b.y.p, e64);
-                        b.apply_op<float>(t, EPI_RESID, true, b.x32.p, b.y32.p, e32);
+                        run64();
+                        run32();
                     }
                     // each precision timed on its own (their kernels differ in
                     // registers and occupancy, so their best depths differ)
                     HTS_HIP(hipEventRecord(e0, b.s));
-                    for (int r = 0; r < 6; r++) b.apply_op<double>(t, EPI_RESID, true, b.inner_x.p, b.y.p, e64);
+                    for (int r = 0; r < 6; r++) run64();
                     HTS_HIP(hipEventRecord(e1, b.s));
-                    for (int r = 0; r < 6; r++) b.apply_op<float>(t, EPI_RESID, true, b.x32.p, b.y32.p, e32);
+                    for (int r = 0; r < 6; r++) run32();
                     HTS_HIP(hipEventRecord(e2, b.s));
                     HTS_HIP(hipEventSynchronize(e2));
                     float ms[2] = {0.0f, 0.0f};
@@ -2308,8 +2355,8 @@ hts_status hts_autotune(hts_mesh *const *meshes, int32_t n)
                     HTS_HIP(hipEventElapsedTime(&ms[1], e1, e2));
                     static const bool verbose = env_or("HTS_VERBOSE", 0.0) > 0.0;
                     if (verbose)
-                        std::fprintf(stderr, "[hts] autotune family %d field %d %dx%dx%d z-depth %d: %d blocks, %.2f us FP64, "
-                                     "%.2f us FP32\n", fam, f, m->N[0], m->N[1], m->N[2], zc, b.work_set<double>(f).n,
+                        std::fprintf(stderr, "[hts] autotune family %d field %d %dx%dx%d z-depth %d: %.2f us FP64, "
+                                     "%.2f us FP32\n", fam, f, m->N[0], m->N[1], m->N[2], zc,
                                      1000.0 / 6 * ms[0], 1000.0 / 6 * ms[1]);
                     // deeper ones only get slower once both are well off their best
                     if (ms[0] > 1.6 * best[0] && ms[1] > 1.6 * best[1]) break;
