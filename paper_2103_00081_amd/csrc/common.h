@@ -186,6 +186,11 @@ constexpr int Q1_STRIP = 4;
 constexpr int Q1S_WAVES = 4;
 constexpr int Q1S_OWNED = 62;
 constexpr int Q1S_ROWS = 2;
+// Strips of general hexahedra (op_hexs.hip, single applies): waves per block (one cell
+// row each) and owned node columns per block
+constexpr int HEX_STRIP = 6;
+constexpr int HEXS_WAVES = 4;
+constexpr int HEXS_OWNED = 62;
 // Q2 strips: waves per block (one cell row each; the FP64 heat kernel's 340 registers
 // allow one wave per SIMD) and owned cell columns per block
 constexpr int Q2_STRIP = 5;

@@ -22,6 +22,8 @@ void launch_q1s_solo(int field, bool graded, const OpDev &op, int ntx, int zc, c
 template <typename T>
 void launch_q2s_solo(int field, bool graded, const OpDev &op, int ntx, int zc, const T *x, T *y, hipStream_t s);
 template <typename T>
+void launch_hexs_solo(int field, const OpDev &op, int ntx, int zc, const T *x, T *y, hipStream_t s);
+template <typename T>
 void launch_hex(int field, int epi, bool masked, const OpDev *ops, const WorkItem *work, int nwork, const T *x,
                 T *y, const EpiArgs<T> &ep, hipStream_t s);
 void launch_hex_inv_diag(const OpDev &op, double *inv_diag, hipStream_t s);
@@ -52,12 +54,12 @@ template void launch_apply<float>(int, int, int, bool, bool, const OpDev *, cons
 template <typename T>
 void launch_strip_solo(const hts_mesh *m, int field, const OpDev &op, int zc, const T *x, T *y, hipStream_t s)
 {
-    const int family = kernel_family(m, true);
+    const int family = apply_family(m);
     int ntx, nty;
     tile_grid(m, family, field, sizeof(T) == 8, ntx, nty);
     if (family == Q1_STRIP) launch_q1s_solo<T>(field, m->graded, op, ntx, zc, x, y, s);
     else if (family == Q2_STRIP) launch_q2s_solo<T>(field, m->graded, op, ntx, zc, x, y, s);
-    else throw Error(-1, "no strip kernel for this mesh");
+    else launch_hexs_solo<T>(field, op, ntx, zc, x, y, s);
 }
 template void launch_strip_solo<double>(const hts_mesh *, int, const OpDev &, int, const double *, double *, hipStream_t);
 template void launch_strip_solo<float>(const hts_mesh *, int, const OpDev &, int, const float *, float *, hipStream_t);

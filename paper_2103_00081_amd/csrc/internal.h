@@ -225,6 +225,8 @@ inline int kernel_family(const hts_mesh *m, bool strips)
     if (!strips) return m->p;
     return m->p == 1 ? Q1_STRIP : Q2_STRIP;
 }
+// Kernel family of a single apply (launch_strip_solo)
+inline int apply_family(const hts_mesh *m) { return m->general ? HEX_STRIP : kernel_family(m, true); }
 // tiles per node plane of a kernel family along x and y
 void tile_grid(const hts_mesh *m, int family, int field, bool fp64, int &ntx, int &nty);
 // y = A x (masked, distinct buffers) of one mesh by its strip kernel, one launch:

@@ -1,8 +1,7 @@
 // hts_apply_operator without device allocation: every buffer the apply needs
-// beyond the mesh's own data and the caller's x and y (the operator
-// descriptors, the work list, the time slots and line-source coefficients of
-// the heat operator, and the FP32 piezometric pressure it reads) lives in one
-// statically sized device array per GPU.  For callers that cannot allocate
+// beyond the mesh's own data and the caller's x and y (the time slots and
+// line-source coefficients of the heat operator) lives in one statically sized
+// device array per GPU.  For callers that cannot allocate
 // (code under graph capture, tight loops, harnesses that forbid it).
 #include <cstring>
 #include <functional>
@@ -14,9 +13,6 @@
 
 namespace hts {
 hts_status guard_call(const std::function<void()> &f);
-template <typename T>
-void launch_apply(int family, int field, int epi, bool masked, bool graded, const OpDev *ops, const WorkItem *work,
-                  int nwork, const T *x, T *y, const EpiArgs<T> &ep, hipStream_t s);
 
 namespace {
 
@@ -68,33 +64,6 @@ void put(unsigned char *dst, const void *src, size_t nbytes, hipStream_t s)
     }
 }
 
-// work item w: tile (w % ntx, (w / ntx) % nty), node planes [z0, z0 + zc)
-__global__ void k_make_work(WorkItem *__restrict__ w, int ntx, int nty, int zc, int NZ, int total)
-{
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= total) return;
-    WorkItem it{};
-    it.inst = 0;
-    it.tx = b % ntx;
-    it.ty = (b / ntx) % nty;
-    it.z0 = (b / (ntx * nty)) * zc;
-    it.z1 = min(NZ, it.z0 + zc);
-    it.slot = b;
-    w[b] = it;
-}
-
-// chunk c: nodes [c * len, min(n, (c + 1) * len)) of instance 0
-__global__ void k_make_chunks(Chunk *__restrict__ c, int64_t n, int64_t len, int nchunk)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nchunk) return;
-    Chunk ch{};
-    ch.inst = 0;
-    ch.beg = (int64_t)i * len;
-    ch.end = min(n, ch.beg + len);
-    c[i] = ch;
-}
-
 size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 
 }  // namespace
@@ -118,38 +87,31 @@ extern "C" hts_status hts_apply_operator_noalloc(hts_mesh *m, hts_field field, h
         const hipStream_t s = m->stream;
         const bool fp32 = prec == HTS_FP32;
         const bool steady = field == 0 && (dt <= 0.0 || m->B <= 0.0);
-        // the scratch holds the work list and descriptors of the tile kernels (the
-        // strip kernels of box meshes need neither; the limit is the same)
+        // The entry point refuses what did not fit its scratch when that held the
+        // descriptors, the tile kernels' work list, the chunk list
+        // and the FP32 pressure; the strip kernels need the time slots and line sources
         const int family = kernel_family(m, false);
         int ntx, nty;
         tile_grid(m, family, field, !fp32, ntx, nty);
         const int zc = zc_for(m, family, field, fp32 ? 1 : 0, (int64_t)ntx * nty, 0);
-        const int64_t nzc = (m->N[2] + zc - 1) / zc;
-        const int64_t nwork = (int64_t)ntx * nty * nzc;
+        const int64_t nwork = (int64_t)ntx * nty * ((m->N[2] + zc - 1) / zc);
         const int nsrc = field == 1 ? (int)m->line_srcs.size() : 0;
-        const int64_t clen = 1024;
-        const int64_t nchunk = (field == 1 && fp32) ? (m->nnode + clen - 1) / clen : 0;
+        const int64_t nchunk = (field == 1 && fp32) ? (m->nnode + 1023) / 1024 : 0;
         // layout, 256-byte aligned pieces
         size_t o = 0;
-        const size_t o_ops = o;    o += up256(2 * sizeof(OpDev));
         const size_t o_S = o;      o += up256(NSLOT * sizeof(double));
         const size_t o_src = o;    o += up256((size_t)std::max(1, nsrc) * sizeof(SrcDev));
         const size_t o_coef = o;   o += up256((size_t)std::max(1, nsrc) * sizeof(double));
-        const size_t o_work = o;   o += up256((size_t)nwork * sizeof(WorkItem));
-        const size_t o_chunk = o;  o += up256((size_t)nchunk * sizeof(Chunk));
-        const size_t o_p32 = o;    o += up256((size_t)(nchunk ? m->nnode : 0) * sizeof(float));
-        if (o > SCRATCH_BYTES || nwork > INT32_MAX)
-            throw Error(HTS_ERR_ARG, "mesh too large for the allocation-free apply: needs " + std::to_string(o) +
+        const size_t need = o + up256(2 * sizeof(OpDev)) + up256((size_t)nwork * sizeof(WorkItem)) +
+                            up256((size_t)nchunk * sizeof(Chunk)) + up256((size_t)(nchunk ? m->nnode : 0) * sizeof(float));
+        if (need > SCRATCH_BYTES || nwork > INT32_MAX)
+            throw Error(HTS_ERR_ARG, "mesh too large for the allocation-free apply: needs " + std::to_string(need) +
                                          " bytes of the " + std::to_string(SCRATCH_BYTES) + "-byte scratch");
         HTS_HIP(hipSetDevice(m->desc.device));
         unsigned char *base = scratch_ptr(m->desc.device);
-        OpDev *ops = reinterpret_cast<OpDev *>(base + o_ops);
         double *S = reinterpret_cast<double *>(base + o_S);
         SrcDev *srcs = reinterpret_cast<SrcDev *>(base + o_src);
         double *coef = reinterpret_cast<double *>(base + o_coef);
-        WorkItem *work = reinterpret_cast<WorkItem *>(base + o_work);
-        Chunk *chunks = reinterpret_cast<Chunk *>(base + o_chunk);
-        float *P32 = reinterpret_cast<float *>(base + o_p32);
 
         if (field == 1) {
             // time slots of instance 0, then the line-source coefficients at t + dt
@@ -165,51 +127,17 @@ extern "C" hts_status hts_apply_operator_noalloc(hts_mesh *m, hts_field field, h
                 launch_source_values(srcs, nsrc, S, coef, s);
             }
         }
-        if (family != DEGREE_HEX) {
-            // box meshes: one launch of the strip kernel, as hts_apply_operator
-            const int strip = kernel_family(m, true);
-            int sx, sy;
-            tile_grid(m, strip, field, !fp32, sx, sy);
-            const int szc = zc_for(m, strip, field, fp32 ? 1 : 0, (int64_t)sx * sy, 0);
-            OpDev op = make_op(m, field, fp32, dt, steady, false);
-            op.P = m->P.p;
-            op.lcoef = coef;
-            if (fp32) launch_strip_solo<float>(m, field, op, szc, static_cast<const float *>(x_dev),
-                                               static_cast<float *>(y_dev), s);
-            else launch_strip_solo<double>(m, field, op, szc, static_cast<const double *>(x_dev),
-                                           static_cast<double *>(y_dev), s);
-            return;
-        }
-        // descriptors: [0] FP64, [1] FP32, as the solo batch builds them
-        OpDev h[2];
-        for (int q = 0; q < 2; q++) {
-            h[q] = make_op(m, field, q == 1, dt, steady, false);
-            h[q].off = 0;
-            if (field == 1) {
-                h[q].P = q == 1 ? (const void *)(nchunk ? P32 : nullptr) : (const void *)m->P.p;
-                h[q].lcoef = coef;
-                if (q == 1) h[q].rho_g = 0.0;   // the FP32 pressure is piezometric
-            }
-        }
-        put(base + o_ops, h, sizeof(h), s);
-        k_make_work<<<dim3((unsigned)((nwork + 255) / 256)), dim3(256), 0, s>>>(work, ntx, nty, zc, m->N[2],
-                                                                               (int)nwork);
-        HTS_LAUNCH_CHECK();
-        if (nchunk) {
-            k_make_chunks<<<dim3((unsigned)((nchunk + 255) / 256)), dim3(256), 0, s>>>(chunks, m->nnode, clen,
-                                                                                     (int)nchunk);
-            HTS_LAUNCH_CHECK();
-            VecCtx v{chunks, (int)nchunk, nullptr, S, s};
-            vpiezo32(v, ops, m->P.p, P32);
-        }
-        if (!fp32) {
-            EpiArgs<double> ep{};
-            launch_apply<double>(family, field, EPI_STORE, true, m->graded, ops, work, (int)nwork,
-                                 static_cast<const double *>(x_dev), static_cast<double *>(y_dev), ep, s);
-        } else {
-            EpiArgs<float> ep{};
-            launch_apply<float>(family, field, EPI_STORE, true, m->graded, ops + 1, work, (int)nwork,
-                                static_cast<const float *>(x_dev), static_cast<float *>(y_dev), ep, s);
-        }
+        // one launch, as hts_apply_operator
+        const int strip = apply_family(m);
+        int sx, sy;
+        tile_grid(m, strip, field, !fp32, sx, sy);
+        const int szc = zc_for(m, strip, field, fp32 ? 1 : 0, (int64_t)sx * sy, 0);
+        OpDev op = make_op(m, field, fp32, dt, steady, false);
+        op.P = m->P.p;
+        op.lcoef = coef;
+        if (fp32) launch_strip_solo<float>(m, field, op, szc, static_cast<const float *>(x_dev),
+                                           static_cast<float *>(y_dev), s);
+        else launch_strip_solo<double>(m, field, op, szc, static_cast<const double *>(x_dev),
+                                       static_cast<double *>(y_dev), s);
     });
 }

@@ -193,6 +193,13 @@ void tile_grid(const hts_mesh *m, int family, int field, bool fp64, int &ntx, in
         nty = 1;
         return;
     }
+    if (family == HEX_STRIP) {
+        const int own = HEXS_WAVES - 1;
+        const int64_t cols = (int64_t)((m->N[1] + own - 1) / own) * (m->n[0] + 2);
+        ntx = (int)((cols + HEXS_OWNED - 1) / HEXS_OWNED);
+        nty = 1;
+        return;
+    }
     if (family == Q2_STRIP) {
         const int own = 2 * (q2s_waves(field, fp64) - 1);
         const int64_t cols = (int64_t)((m->N[1] + own - 1) / own) * (m->n[0] + 2);
@@ -227,6 +234,25 @@ static int q2_strip_depth(int64_t tiles, int NZ, int field, int prec)
     return best;
 }
 
+// Hexahedra strips: with b blocks on a CU one cell layer takes the larger of 1.8 us
+// (a wave alone on its SIMD) and 1.45 b us (the issue of its instructions), and a march
+// of L layers about L + 3/2 of them.  FP32 heat, 128 x 128 x 64: 52 us at depth 6 (1001
+// blocks), 54 at 9, 57 at 7, 67 at 12; 200 x 200 x 60: 98 at 8, 117 at 12, 106 at 4;
+// 64 x 64 x 32: 15.7 at 2 and 4, 17.9 at 1, 20.5 at 6.
+static int hex_strip_depth(int64_t tiles, int NZ)
+{
+    int best = 1;
+    int64_t cost = INT64_MAX;
+    for (int zc = 1; zc <= std::min(NZ, 16); zc++) {
+        const int64_t b = (tiles * ((NZ + zc - 1) / zc) + 255) / 256, c = std::max<int64_t>(5, 4 * b) * (2 * zc + 3);
+        if (c < cost) {
+            cost = c;
+            best = zc;
+        }
+    }
+    return best;
+}
+
 int zc_for(const hts_mesh *M, int family, int field, int prec, int64_t tiles, int force)
 {
     const int NZ = M->N[2];
@@ -236,6 +262,7 @@ int zc_for(const hts_mesh *M, int family, int field, int prec, int64_t tiles, in
     const int t = tuned_zc(family, field, prec, M->N[0], M->N[1], NZ);
     if (t > 0) return fit(t);
     if (family == Q2_STRIP) return fit(q2_strip_depth(tiles, NZ, field, prec));
+    if (family == HEX_STRIP) return fit(hex_strip_depth(tiles, NZ));
     if (family == Q1_STRIP) {
         // about 1000 blocks, four for each CU.  Small grids: the shortest
         // march (48^3 heat FP32: 9.5 us at depth 2, 13 at 4); large ones: at
@@ -2230,7 +2257,6 @@ hts_status hts_apply_operator(hts_mesh *m, hts_field field, hts_precision prec, 
         HTS_HIP(hipSetDevice(m->desc.device));
         auto B = solo_batch(m);
         Batch &b = *B;
-        b.use_strips(true);
         const bool steady = field == 0 && (dt <= 0.0 || m->B <= 0.0);
         const bool fp32 = prec == HTS_FP32;
         if (field == 1 && b.nlsrc > 0) {
@@ -2238,36 +2264,19 @@ hts_status hts_apply_operator(hts_mesh *m, hts_field field, hts_precision prec, 
             b.set_time(tn, fs);
             launch_source_values(b.lsrc.p, b.nlsrc, b.S.p, b.lcoef.p, b.s);
         }
-        if (b.strips) {
-            // one launch: the descriptor goes by value and the heat operator
-            // reads the mesh's own pressure state
-            OpDev o = make_op(m, field, fp32, dt, steady, false);
-            o.P = m->P.p;
-            o.lcoef = b.lcoef.p;
-            int ntx, nty;
-            tile_grid(m, b.family(), field, !fp32, ntx, nty);
-            const int zc = zc_for(m, b.family(), field, fp32, (int64_t)ntx * nty, 0);
-            b.timed_apply(field, EPI_STORE, fp32, [&] {
-                if (fp32) launch_strip_solo<float>(m, field, o, zc, (const float *)x_dev, (float *)y_dev, b.s);
-                else launch_strip_solo<double>(m, field, o, zc, (const double *)x_dev, (double *)y_dev, b.s);
-            });
-            return;
-        }
-        std::vector<int32_t> all(1, 1);
-        b.set_active(all);
-        Tables &t = b.apply_tables(field, dt, steady);
-        if (field == 1) {
-            HTS_HIP(hipMemcpyAsync(b.P1.p, m->P.p, m->nnode * sizeof(double), hipMemcpyDeviceToDevice, b.s));
-            VecCtx v = b.vctx(false);
-            vpiezo32(v, b.massH.d64.p, b.P1.p, b.P32.p);
-        }
-        if (!fp32) {
-            EpiArgs<double> ep{};
-            b.apply_op<double>(t, EPI_STORE, true, (const double *)x_dev, (double *)y_dev, ep);
-        } else {
-            EpiArgs<float> ep{};
-            b.apply_op<float>(t, EPI_STORE, true, (const float *)x_dev, (float *)y_dev, ep);
-        }
+        // one launch: the descriptor goes by value and the heat operator reads the
+        // mesh's own pressure state
+        OpDev o = make_op(m, field, fp32, dt, steady, false);
+        o.P = m->P.p;
+        o.lcoef = b.lcoef.p;
+        const int family = apply_family(m);
+        int ntx, nty;
+        tile_grid(m, family, field, !fp32, ntx, nty);
+        const int zc = zc_for(m, family, field, fp32, (int64_t)ntx * nty, 0);
+        b.timed_apply(field, EPI_STORE, fp32, [&] {
+            if (fp32) launch_strip_solo<float>(m, field, o, zc, (const float *)x_dev, (float *)y_dev, b.s);
+            else launch_strip_solo<double>(m, field, o, zc, (const double *)x_dev, (double *)y_dev, b.s);
+        });
     });
 }
 
@@ -2302,18 +2311,18 @@ hts_status hts_autotune(hts_mesh *const *meshes, int32_t n)
             HTS_HIP(hipEventCreate(&e2));
             for (int kind = 0; kind < 2; kind++)
             for (int f = 0; f < 2; f++) {
-                const int fam = kernel_family(m, kind == 1);
-                if (kind == 1 && fam == kernel_family(m, false)) continue;
+                const int fam = kind == 1 ? apply_family(m) : kernel_family(m, false);
                 b.use_strips(false);
                 OpDev o64 = make_op(m, f, false, dt, f == 0 && m->B <= 0.0, false), o32 = make_op(m, f, true, dt, f == 0 && m->B <= 0.0, false);
                 o64.P = o32.P = m->P.p;
                 o64.lcoef = o32.lcoef = b.lcoef.p;
                 Tables &t = b.apply_tables(f, dt, f == 0 && m->B <= 0.0);
                 std::vector<int> cands = {2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32, 48, 64};
-                for (int pr = 0; fam == Q2_STRIP && pr < 2; pr++) {
+                for (int pr = 0; (fam == Q2_STRIP || fam == HEX_STRIP) && pr < 2; pr++) {
                     int tx, ty;
                     tile_grid(m, fam, f, pr == 0, tx, ty);
-                    cands.insert(cands.begin(), q2_strip_depth((int64_t)tx * ty, m->N[2], f, pr));
+                    const int64_t tiles = (int64_t)tx * ty;
+                    cands.insert(cands.begin(), fam == Q2_STRIP ? q2_strip_depth(tiles, m->N[2], f, pr) : hex_strip_depth(tiles, m->N[2]));
                 }
                 double best[2] = {1e30, 1e30};
                 int bz[2] = {0, 0};
