@@ -9,8 +9,6 @@ void gm_begin(int ninst, int32_t *active, double *S, double *g, int mres, int32_
 // the squared norm of w after the first projection (entry j+1)
 void gm_solve(int ninst, const int32_t *cyc, int mres, const double *H, const double *g, const int32_t *kdim,
               double *y, hipStream_t s);
-void outer_check(int ninst, int32_t *active, double *S, const double *rr, hipStream_t s);
-void set_inner_tol(int ninst, const int32_t *active, double *S, double floor2, double factor2, hipStream_t s);
 void convert_plain(int64_t n, const double *in, float *out, hipStream_t s);
 // Fallback rule of the learned preconditioner, on the device (one thread per
 // instance): nn_gate_init clears an inner solve's history; nn_gate_begin,
@@ -24,6 +22,5 @@ void nn_gate_begin(int ninst, const int32_t *active, double *S, int32_t *use_nn,
                    int32_t *act_save, hipStream_t s);
 void nn_gate_check(int ninst, double *S, int32_t *use_nn, int32_t *use_mg, int32_t *active, hipStream_t s);
 void nn_gate_end(int ninst, const int32_t *act_save, int32_t *active, hipStream_t s);
-void set_otol(int ninst, const int32_t *active, double *S, const double *bb, int stride, double rtol2, hipStream_t s);
 
 }  // namespace hts

@@ -53,50 +53,6 @@ __global__ void k_gm_solve(int ninst, const int32_t *cyc, int mres, const double
     }
 }
 
-// outer defect correction: v0 = ||b - A x||^2
-__global__ void k_outer_check(int ninst, int32_t *active, double *S, const double *rr)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ninst || !active[i]) return;
-    double *Si = S + (int64_t)i * NSLOT;
-    const double v = rr[i];
-    Si[S_ORR] = v;
-    Si[S_ONORM] = sqrt(fmax(v, 0.0));
-    Si[S_OINV] = v > 0.0 ? 1.0 / sqrt(v) : 0.0;
-    if (!isfinite(v)) {
-        Si[S_OSTATUS] = -6;
-        active[i] = 0;
-    } else if (v <= Si[S_OTOL2]) {
-        Si[S_OSTATUS] = 0;
-        active[i] = 0;
-    }
-}
-
-__global__ void k_set_otol(int ninst, const int32_t *active, double *S, const double *bb, int stride, double rtol2)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ninst || (active && !active[i])) return;
-    double *Si = S + (int64_t)i * NSLOT;
-    const double v = bb[(int64_t)i * stride];
-    Si[S_OBB] = v;
-    Si[S_OTOL2] = rtol2 * v;
-    Si[S_OSTATUS] = 1;
-}
-
-// inner tolerance of a defect-correction solve whose RHS is r / ||r||:
-// TOL2 = max(floor2, factor2 * OTOL2 / ORR)
-__global__ void k_set_inner_tol(int ninst, const int32_t *active, double *S, double floor2, double factor2)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ninst || (active && !active[i])) return;
-    double *Si = S + (int64_t)i * NSLOT;
-    const double rel = Si[S_ORR] > 0.0 ? Si[S_OTOL2] / Si[S_ORR] : 1.0;
-    Si[S_BB] = 1.0;
-    Si[S_TOL2] = fmax(floor2, factor2 * rel);
-    Si[S_ITER] = 0.0;
-    Si[S_STATUS] = 1.0;
-}
-
 // Learned preconditioner: after two consecutive network-preconditioned
 // iterations that each leave ||r_{k+1}||^2 > 0.81 ||r_k||^2 (a residual
 // norm reduction weaker than 0.9), or on a non-finite residual or network
@@ -176,12 +132,6 @@ __global__ void k_convert_plain_df(int64_t n, const double *in, float *out)
 
 }  // namespace
 
-void set_inner_tol(int ninst, const int32_t *active, double *S, double floor2, double factor2, hipStream_t s)
-{
-    k_set_inner_tol<<<dim3((ninst + 63) / 64), dim3(64), 0, s>>>(ninst, active, S, floor2, factor2);
-    HTS_LAUNCH_CHECK();
-}
-
 static dim3 inst_grid(int ninst) { return dim3((unsigned)((ninst + 63) / 64)); }
 
 void nn_gate_init(int ninst, double *S, hipStream_t s)
@@ -227,16 +177,6 @@ void gm_solve(int ninst, const int32_t *cyc, int mres, const double *H, const do
               double *y, hipStream_t s)
 {
     k_gm_solve<<<g1(ninst), dim3(64), 0, s>>>(ninst, cyc, mres, H, g, kdim, y);
-    HTS_LAUNCH_CHECK();
-}
-void outer_check(int ninst, int32_t *active, double *S, const double *rr, hipStream_t s)
-{
-    k_outer_check<<<g1(ninst), dim3(64), 0, s>>>(ninst, active, S, rr);
-    HTS_LAUNCH_CHECK();
-}
-void set_otol(int ninst, const int32_t *active, double *S, const double *bb, int stride, double rtol2, hipStream_t s)
-{
-    k_set_otol<<<g1(ninst), dim3(64), 0, s>>>(ninst, active, S, bb, stride, rtol2);
     HTS_LAUNCH_CHECK();
 }
 

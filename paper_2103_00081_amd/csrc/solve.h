@@ -106,6 +106,7 @@ struct Batch {
         RedCtx red{};
     };
     WorkSet ws[2][2][2];
+    bool flags_all = false;    // activate_all set the device flags, nothing has changed them
     bool strips = false;       // kernel choice of the current call (use_strips on entry)
     int zc_force[2][2] = {{0, 0}, {0, 0}};
     int family() const { return kernel_family(m[0], strips); }
@@ -196,6 +197,9 @@ struct Batch {
     ~Batch();
     void build_work(int kind);
     void use_strips(bool allowed);
+    // every device flag set; no launch where this did so last (no set_active and
+    // no solve since)
+    void activate_all();
     void make_tables(Tables &t, int field, double dt, bool steady, bool mass_only);
     Tables &apply_tables(int field, double dt, bool steady)
     {
@@ -237,12 +241,13 @@ struct Batch {
     template <typename T> void tmass_prec(Hier &H, const T *b, T *x);
     void build_tmass(Hier &H, double dt);
     template <typename T>
-    // x0_zero: x holds zeros on entry, so the initial residual is b itself
+    // started: vinner_start has set x = 0 and the initial residual (r, or the first
+    // basis vector) to b, and left the partial sums of b.b
     int cg(const Tables &A, const std::function<void(const T *, T *)> &M, const T *b, T *x, int maxit, bool flexible,
-           int check_every, bool x0_zero = false);
+           int check_every, bool started = false);
     template <typename T>
     void fgmres(const Tables &A, const std::function<void(const T *, T *)> &M, const T *b, T *x, int maxit, int mres,
-                int check_every, bool x0_zero = false);
+                int check_every, bool started = false);
     void ensure_gmres(int mres);
 
     FieldStats solve_field(int field, Hier *mg, const Tables &A, double *b64, double *x64, const hts_solver_opts &o,
@@ -251,8 +256,11 @@ struct Batch {
                   const std::vector<double> *xtra = nullptr, const std::vector<double> *xtra2 = nullptr);
     void xtra_factors(int field, double dt, const hts_solver_opts &o, std::vector<double> &c1,
                       std::vector<double> &c2) const;
+    // right-hand side b, initial guess x and the partial sums of b.b
     void pressure_rhs(Hier &H, bool steady);
     void heat_rhs(Hier &H);
+    void finish_rhs(int f, Hier &H, const double *b0, const double *ld, const double *Xn, const double *Xp,
+                    const double *Xpp);
     void gather_state();
     void scatter_state();
     FieldStats solve_pressure(double dt, bool steady_all, const hts_solver_opts &o);

@@ -542,7 +542,17 @@ void Batch::download_S()
     slots_from_export();
 }
 void Batch::slots_from_export() { std::memcpy(hS, hexpS, sizeof(double) * n * NSLOT); }
-void Batch::set_active(const std::vector<int32_t> &a) { vset_flags(a.data(), n, active.p, s); }
+void Batch::set_active(const std::vector<int32_t> &a)
+{
+    vset_flags(a.data(), n, active.p, s);
+    flags_all = false;
+}
+void Batch::activate_all()
+{
+    if (flags_all) return;
+    set_active(std::vector<int32_t>(n, 1));
+    flags_all = true;
+}
 std::vector<int32_t> Batch::get_active()
 {
     export_state();
@@ -1439,7 +1449,7 @@ void Batch::cheb_prec(Hier &H, const T *b, T *x)
 // ------------------------------------------------------------------- CG
 template <typename T>
 int Batch::cg(const Tables &A, const std::function<void(const T *, T *)> &M, const T *b, T *x, int maxit,
-              bool flexible, int check_every, bool x0_zero)
+              bool flexible, int check_every, bool started)
 {
     T *r = PK(T, this->r, r32), *z = PK(T, this->z, z32), *pv = PK(T, pp, p32), *q = PK(T, this->q, q32);
     T *ro = flexible ? PK(T, rold, rold32) : nullptr;
@@ -1448,10 +1458,8 @@ int Batch::cg(const Tables &A, const std::function<void(const T *, T *)> &M, con
     ep.b = b;
     ep.partial = partial.p;
     exported_last = false;
-    if (x0_zero) {
-        // r = b - A 0 = b: a copy and a norm instead of an operator pass
-        vcopy<T>(v, b, r);
-        vdot<T>(v, b, b, nullptr, partial.p);
+    flags_all = false;
+    if (started) {
         vreduce(rch, partial.p, 2, RED_CG_INIT, 0, S.p, active.p, maxit, 0.0, nullptr, s);
     } else {
         apply_op<T>(A, EPI_RESID_NORM, true, x, r, ep);
@@ -1555,7 +1563,7 @@ int Batch::cg(const Tables &A, const std::function<void(const T *, T *)> &M, con
 // ---------------------------------------------------------------- FGMRES
 template <typename T>
 void Batch::fgmres(const Tables &A, const std::function<void(const T *, T *)> &M, const T *b, T *x, int maxit,
-                   int mres, int check_every, bool x0_zero)
+                   int mres, int check_every, bool started)
 {
     ensure_gmres(mres);
     T *V = PK(T, V64, V32), *Z = PK(T, Z64, Z32);
@@ -1565,10 +1573,7 @@ void Batch::fgmres(const Tables &A, const std::function<void(const T *, T *)> &M
         EpiArgs<T> ep{};
         ep.b = b;
         ep.partial = partial.p;
-        if (x0_zero && cycle == 0) {
-            // V_0 = b - A 0 = b
-            vcopy<T>(v, b, V);
-            vdot<T>(v, b, b, nullptr, partial.p);
+        if (started && cycle == 0) {
             vreduce(rch, partial.p, 2, RED_STORE, S_RR, S.p, active.p, 0, 0.0, nullptr, s);
         } else {
             apply_op<T>(A, EPI_RESID_NORM, true, x, V, ep);
@@ -1711,11 +1716,10 @@ FieldStats Batch::solve_field(int field, Hier *mg, const Tables &A, double *b64,
     HTS_HIP(hipEventCreate(&e1));
     HTS_HIP(hipEventRecord(e0, s));
     // the device flags equal participants on entry: both callers set them
-    // with the right-hand side, and nothing launched since changes them
-    VecCtx vall = vctx();
-    vdot<double>(vall, b64, b64, nullptr, partial.p);
-    vreduce(rch, partial.p, 2, RED_NONE, 0, S.p, active.p, 0, 0.0, redout.p, s);
-    set_otol(n, active.p, S.p, redout.p, 2, rtol * rtol, s);
+    // with the right-hand side, whose last launch also left the partial sums
+    // of b.b; nothing launched since changes them
+    flags_all = false;
+    vreduce(rch, partial.p, 2, RED_OTOL, 0, S.p, active.p, 0, rtol * rtol, nullptr, s);
     std::vector<int32_t> outer = participants;
     int total_inner = 0;
     bool fresh = false;   // the last export holds the final slots
@@ -1728,13 +1732,15 @@ FieldStats Batch::solve_field(int field, Hier *mg, const Tables &A, double *b64,
         ep.b = b64;
         ep.partial = partial.p;
         apply_op<double>(A, EPI_RESID_NORM, true, x64, this->y.p, ep);
-        vreduce(work_set<double>(A.field).red, partial.p, 1, RED_NONE, 0, S.p, active.p, 0, 0.0, redout.p, s);
-        outer_check(n, active.p, S.p, redout.p, s);
+        // inner tolerance: by the norm of the outer residual, above what FP32 can reach
+        const double fl = fp32 ? std::pow(std::max(o.inner_rtol, 1e-6), 2) : 0.0;
+        const bool defer = oit == 0 && !learned;
+        vreduce(work_set<double>(A.field).red, partial.p, 1, defer ? RED_OUTER_INNER : RED_OUTER, 0, S.p, active.p, 0, fl,
+                nullptr, s);
         HTS_HIP(hipEventRecord(e1, s));
         // The first check is read back with the inner solve's last export
         // (the inner kernels skip the instances it deactivated), which saves
         // a host round trip; later checks are read at once.
-        const bool defer = oit == 0 && !learned;
         const std::vector<int32_t> prev = outer;
         if (!defer) {
             outer = get_active();
@@ -1748,12 +1754,12 @@ FieldStats Batch::solve_field(int field, Hier *mg, const Tables &A, double *b64,
         }
         // inner system: A d = r / ||r||
         hist_tag = oit;
-        const double fl = fp32 ? std::pow(std::max(o.inner_rtol, 1e-6), 2) : 0.0;
-        set_inner_tol(n, active.p, S.p, fl, 0.25, s);
+        if (!defer) set_inner_tol(n, active.p, S.p, fl, s);
+        const int mres = std::max(2, std::min(o.gmres_restart, 60));
+        if (field == 1) ensure_gmres(mres);
         VecCtx v = vctx();
         if (fp32) {
-            vconvert<double, float>(v, 1.0, S_OINV, this->y.p, b32.p);
-            vfill<float>(v, x32.p, 0.0f);
+            vinner_start<float>(v, this->y.p, S_OINV, b32.p, x32.p, field == 0 ? r32.p : V32.p, partial.p);
             auto M = [&](const float *r_, float *z_) {
                 if (mg) vcycle<float>(*mg, 0, r_, z_);
                 else if (hprec->tensor) tmass_prec<float>(*hprec, r_, z_);
@@ -1761,12 +1767,12 @@ FieldStats Batch::solve_field(int field, Hier *mg, const Tables &A, double *b64,
             };
             graph_tag = (mg ? "mg" : "cheb") + std::to_string((uintptr_t)(mg ? mg : hprec));
             if (field == 0) cg<float>(A, M, b32.p, x32.p, maxit, false, o.check_every, true);
-            else fgmres<float>(A, M, b32.p, x32.p, maxit, std::max(2, std::min(o.gmres_restart, 60)), o.check_every,
-                                 true);
+            else fgmres<float>(A, M, b32.p, x32.p, maxit, mres, o.check_every, true);
         } else {
             // inner RHS r / ||r||; the Krylov work vectors are r, z, pp, q, rold
-            vaxpby<double>(v, 1.0, S_OINV, this->y.p, 0.0, -1, inner_b.p);
-            vfill<double>(v, inner_x.p, 0.0);
+            auto start = [&] {
+                vinner_start<double>(v, this->y.p, S_OINV, inner_b.p, inner_x.p, field == 0 ? r.p : V64.p, partial.p);
+            };
             auto M = [&](const double *r_, double *z_) {
                 if (mg) vcycle<double>(*mg, 0, r_, z_);
                 else if (hprec->tensor) tmass_prec<double>(*hprec, r_, z_);
@@ -1811,14 +1817,17 @@ FieldStats Batch::solve_field(int field, Hier *mg, const Tables &A, double *b64,
                     vcycle<double>(*mg, 0, r_, z_);   // the fallback instances only
                     nn_gate_end(n, act_save.p, active.p, s);
                 };
+                start();
                 cg<double>(A, ML, inner_b.p, inner_x.p, maxit, true, 1, true);
                 chunk_mode = nullptr;
                 chunk_cap = 0;
             } else if (field == 0) {
+                start();
                 cg<double>(A, M, inner_b.p, inner_x.p, maxit, false, o.check_every, true);
-            } else
-                fgmres<double>(A, M, inner_b.p, inner_x.p, maxit, std::max(2, std::min(o.gmres_restart, 60)),
-                               o.check_every, true);
+            } else {
+                start();
+                fgmres<double>(A, M, inner_b.p, inner_x.p, maxit, mres, o.check_every, true);
+            }
         }
         if (inner_hook && field == 0 && !fp32) {
             inner_hook(A, inner_x.p);
@@ -1855,8 +1864,7 @@ FieldStats Batch::solve_field(int field, Hier *mg, const Tables &A, double *b64,
         if (stop) {
             // final judge with the last update
             apply_op<double>(A, EPI_RESID_NORM, true, x64, this->y.p, ep);
-            vreduce(work_set<double>(A.field).red, partial.p, 1, RED_NONE, 0, S.p, active.p, 0, 0.0, redout.p, s);
-            outer_check(n, active.p, S.p, redout.p, s);
+            vreduce(work_set<double>(A.field).red, partial.p, 1, RED_OUTER, 0, S.p, active.p, 0, 0.0, nullptr, s);
             HTS_HIP(hipEventRecord(e1, s));
             outer = get_active();
             fresh = true;
@@ -1925,32 +1933,37 @@ void Batch::xtra_factors(int field, double dt, const hts_solver_opts &o, std::ve
 
 void Batch::pressure_rhs(Hier &H, bool steady)
 {
-    std::vector<int32_t> all(n, 1);
-    set_active(all);
+    activate_all();
     VecCtx v = vctx(false);
     launch_dirichlet_values(H.ops.d64.p, bc[0].p, ch.p, nch, S.p, g.p, s);
     EpiArgs<double> ep{};
     if (!steady) apply_op<double>(massP, EPI_STORE, false, Pn.p, b.p, ep);
-    else vfill<double>(v, b.p, 0.0);
     apply_op<double>(H.ops, EPI_STORE, false, g.p, y.p, ep);
-    vrhs_combine(v, y.p, ld0.p, S_FSCALE, b.p);
-    launch_sources(srows[0].p, srowptr[0].p, sents[0].p, nsrows[0], ssrc[0].p, S.p, b.p, s);
-    vmask<double>(v, H.ops.d64.p, b.p, 0.0);
+    finish_rhs(0, H, steady ? nullptr : b.p, ld0.p, Pn.p, Pp.p, Ppp.p);
 }
 
 void Batch::heat_rhs(Hier &H)
 {
-    std::vector<int32_t> all(n, 1);
-    set_active(all);
-    VecCtx v = vctx(false);
+    activate_all();
     launch_source_values(lsrc.p, nlsrc, S.p, lcoef.p, s);
     launch_dirichlet_values(H.ops.d64.p, bc[1].p, ch.p, nch, S.p, g.p, s);
     EpiArgs<double> ep{};
     apply_op<double>(massH, EPI_STORE, false, Tn.p, b.p, ep);
     apply_op<double>(H.ops, EPI_STORE, false, g.p, y.p, ep);
-    vrhs_combine(v, y.p, ld1.p, S_FSCALE, b.p);
-    launch_sources(srows[1].p, srowptr[1].p, sents[1].p, nsrows[1], ssrc[1].p, S.p, b.p, s);
-    vmask<double>(v, H.ops.d64.p, b.p, 0.0);
+    finish_rhs(1, H, b.p, ld1.p, Tn.p, Tp.p, Tpp.p);
+}
+
+// b = (b0 - y) + S_FSCALE ld + sources, masked; x the initial guess; b.b
+void Batch::finish_rhs(int f, Hier &H, const double *b0, const double *ld, const double *Xn, const double *Xp,
+                       const double *Xpp)
+{
+    VecCtx v = vctx(false);
+    const bool src = nsrows[f] > 0;
+    if (src) {
+        vrhs_combine(v, b0, y.p, ld, S_FSCALE, b.p);
+        launch_sources(srows[f].p, srowptr[f].p, sents[f].p, nsrows[f], ssrc[f].p, S.p, b.p, s);
+    }
+    vrhs_finish(v, H.ops.d64.p, b0, src ? nullptr : y.p, ld, S_FSCALE, b.p, S_XTRA, S_XTRA2, Xn, Xp, Xpp, x.p, partial.p);
 }
 
 // State in and out of the batch vectors, one launch per field for up to 128
@@ -2044,12 +2057,9 @@ FieldStats Batch::solve_pressure(double dt, bool steady_all, const hts_solver_op
     set_time(tn, fs, &xf, &xf2);
     Hier &H = pressure_hier(steady, dt, o);
     pressure_rhs(H, steady);
-    VecCtx v = vctx(false);
-    vextrapolate(v, S_XTRA, S_XTRA2, H.ops.d64.p, Pn.p, Pp.p, Ppp.p, x.p);
     std::vector<int32_t> all(n, 1);
     FieldStats st = solve_field(0, &H, H.ops, b.p, x.p, o, all, nullptr);
-    std::vector<int32_t> a(n, 1);
-    set_active(a);
+    activate_all();
     vadd(vctx(false), x.p, g.p, P1.p);
     return st;
 }
@@ -2073,9 +2083,8 @@ FieldStats Batch::solve_heat(double dt, const hts_solver_opts &o)
     launch_source_values(lsrc.p, nlsrc, S.p, lcoef.p, s);
     Hier &H = heat_prec(dt, o);
     heat_rhs(H);
-    vextrapolate(v, S_XTRA, S_XTRA2, H.ops.d64.p, Tn.p, Tp.p, Tpp.p, x.p);
     FieldStats st = solve_field(1, H.multigrid ? &H : nullptr, H.ops, b.p, x.p, o, all, &H);
-    set_active(all);
+    activate_all();
     vadd(vctx(false), x.p, g.p, T1.p);
     return st;
 }
@@ -2105,11 +2114,7 @@ int Batch::step(double dt, const hts_solver_opts &o, std::vector<hts_step_stats>
         }
     }
     if (rc == HTS_OK) {
-        std::vector<int32_t> all(n, 1);
-        set_active(all);
-        VecCtx v = vctx(false);
-        vshift(v, P1.p, Pn.p, Pp.p, Ppp.p);
-        vshift(v, T1.p, Tn.p, Tp.p, Tpp.p);
+        vshift(vctx(false), ShiftArgs{{P1.p, T1.p}, {Pn.p, Tn.p}, {Pp.p, Tp.p}, {Ppp.p, Tpp.p}});
         for (int i = 0; i < n; i++) {
             m[i]->t += dt;
             for (int f = 0; f < 2; f++) {

@@ -39,7 +39,10 @@ enum RedOp {
     RED_CG_INIT = 6,           // RR = RR0 = v0, ITER = 0, converged if RR <= TOL2
     RED_SET_TOL = 7,           // BB = v0, TOL2 = aux * v0
     RED_INVSQRT = 8,           // S[slot] = v0, S[slot+1] = 1/sqrt(v0)
-    RED_ARNOLDI = 9            // FGMRES column update (vreduce_arnoldi)
+    RED_ARNOLDI = 9,           // FGMRES column update (vreduce_arnoldi)
+    RED_OTOL = 10,             // OBB = v0, OTOL2 = aux v0, OSTATUS = 1
+    RED_OUTER = 11,            // ORR = v0, its root and inverse root; done if v0 <= OTOL2
+    RED_OUTER_INNER = 12       // and, if not done, the tolerance of the inner solve (set_inner_tol; floor2 = aux)
 };
 
 template <typename T> void vfill(const VecCtx &v, T *y, T val);
@@ -65,17 +68,27 @@ void vbasis_update(const VecCtx &v, const T *Z, int64_t ld, const int32_t *kdim,
                    double scale, int iscale, TX *x);
 template <typename TX, typename TY> void vconvert(const VecCtx &v, double sc, int ic, const TX *x, TY *y);
 template <typename T> void vadd_scaled(const VecCtx &v, double sc, int ic, const T *d, double *x);
-// x = Xn + c1 (Xn - Xp) + c2 (Xp - Xpp), c1 = S[slot1], c2 = S[slot2] per
-// instance (Xp read only if a factor is nonzero, Xpp only if c2 is); 0 at
-// the constrained nodes of ops when ops is given
-void vextrapolate(const VecCtx &v, int slot1, int slot2, const OpDev *ops, const double *Xn, const double *Xp,
-                  const double *Xpp, double *x);
-// b = (b - y) + S[slot] ld
-void vrhs_combine(const VecCtx &v, const double *y, const double *ld, int slot, double *b);
+// b = (b0 - y) + S[slot] ld (b0 null: 0)
+void vrhs_combine(const VecCtx &v, const double *b0, const double *y, const double *ld, int slot, double *b);
+// b = (b0 - y) + S[slot] ld (y null: b as it is), 0 at the constrained nodes of ops;
+// x = Xn + c1 (Xn - Xp) + c2 (Xp - Xpp), c1 = S[slot1], c2 = S[slot2] per instance (Xp
+// read only if a factor is nonzero, Xpp only if c2 is), 0 at the constrained nodes;
+// partial = b.b as vdot's.  Every instance takes part.
+void vrhs_finish(const VecCtx &v, const OpDev *ops, const double *b0, const double *y, const double *ld, int slot, double *b,
+                 int slot1, int slot2, const double *Xn, const double *Xp, const double *Xpp, double *x, double *partial);
+// b = r = S[ic] y, x = 0, partial = b.b as vdot's
+template <typename T>
+void vinner_start(const VecCtx &v, const double *y, int ic, T *b, T *x, T *r, double *partial);
+// per instance: BB = 1, TOL2 = max(floor2, OTOL2 / (4 ORR)), ITER = 0, STATUS = 1
+void set_inner_tol(int ninst, const int32_t *active, double *S, double floor2, hipStream_t s);
 // z = x + y
 void vadd(const VecCtx &v, const double *x, const double *y, double *z);
-// time-level shift: Xpp = Xp, Xp = Xn, Xn = X1
-void vshift(const VecCtx &v, const double *X1, double *Xn, double *Xp, double *Xpp);
+// time-level shift of both fields: Xpp = Xp, Xp = Xn, Xn = X1
+struct ShiftArgs {
+    const double *X1[2];
+    double *Xn[2], *Xp[2], *Xpp[2];
+};
+void vshift(const VecCtx &v, const ShiftArgs &f);
 template <typename T> void vmask(const VecCtx &v, const OpDev *ops, T *y, T val);
 
 // P32 = (P - P[node 0 of the instance]) + rho_w g z (FP32 heat operator input)

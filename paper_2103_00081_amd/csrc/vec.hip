@@ -385,45 +385,13 @@ __global__ __launch_bounds__(VB) void k_add_scaled(const Chunk *__restrict__ chu
         if (l.in[u]) x[l.e[u]] = xv[u] + c * (double)dv[u];
 }
 
-// Initial guess from the last time levels: x = Xn + c1 (Xn - Xp) +
-// c2 (Xp - Xpp), c1 = S[slot1], c2 = S[slot2] of the instance; with both 0
-// it copies Xn (the older levels are then not read); constrained nodes of
-// ops (if given) get 0.
-__global__ __launch_bounds__(VB) void k_extrapolate(const Chunk *__restrict__ chunks, const int32_t *active,
-                                                    const double *S, int slot1, int slot2,
-                                                    const OpDev *__restrict__ ops, const double *__restrict__ Xn,
-                                                    const double *__restrict__ Xp, const double *__restrict__ Xpp,
-                                                    double *__restrict__ x)
-{
-    CHUNK_PROLOGUE
-    const double c1 = Si[slot1], c2 = Si[slot2];
-    const bool lin = c1 != 0.0 || c2 != 0.0, quad = c2 != 0.0;
-    const Lanes l = chunk_lanes(ch);
-    double a[EPT], b[EPT], q[EPT];
-#pragma unroll
-    for (int u = 0; u < EPT; u++) {
-        a[u] = Xn[l.c[u]];
-        b[u] = lin ? Xp[l.c[u]] : 0.0;
-        q[u] = quad ? Xpp[l.c[u]] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < EPT; u++)
-        if (l.in[u]) {
-            double v = a[u];
-            if (lin) v = a[u] + c1 * (a[u] - b[u]);
-            if (quad) v += c2 * (b[u] - q[u]);
-            if (ops) {
-                const OpDev &o = ops[ch.inst];
-                if (node_constrained(o, l.e[u] - o.off)) v = 0.0;
-            }
-            x[l.e[u]] = v;
-        }
-}
+// Right-hand side assembly: b = (b0 - y) + c ld, c = S[slot] of the instance
+// (b0 null: 0)
+__device__ __forceinline__ double combine_rhs(double c, double ld, double b, double y) { return c * ld + (b - y); }
 
-// Right-hand side assembly: b = (b - y) + c ld, c = S[slot] of the instance
 __global__ __launch_bounds__(VB) void k_rhs_combine(const Chunk *__restrict__ chunks, const int32_t *active,
-                                                    const double *S, const double *__restrict__ y,
-                                                    const double *__restrict__ ld, int slot, double *__restrict__ b)
+                                                    const double *S, const double *b0, const double *__restrict__ y,
+                                                    const double *__restrict__ ld, int slot, double *b)
 {
     CHUNK_PROLOGUE
     const double c = Si[slot];
@@ -431,13 +399,101 @@ __global__ __launch_bounds__(VB) void k_rhs_combine(const Chunk *__restrict__ ch
     double bv[EPT], yv[EPT], lv[EPT];
 #pragma unroll
     for (int u = 0; u < EPT; u++) {
-        bv[u] = b[l.c[u]];
+        bv[u] = b0 ? b0[l.c[u]] : 0.0;
         yv[u] = y[l.c[u]];
         lv[u] = ld[l.c[u]];
     }
 #pragma unroll
     for (int u = 0; u < EPT; u++)
-        if (l.in[u]) b[l.e[u]] = c * lv[u] + (bv[u] - yv[u]);
+        if (l.in[u]) b[l.e[u]] = combine_rhs(c, lv[u], bv[u], yv[u]);
+}
+
+// The end of a right-hand side and the start of its solve, in one pass: b (with
+// COMBINE formed as k_rhs_combine does) is 0 at the constrained nodes, partial = b.b
+// as k_dot's, and the initial guess from the last time levels x = Xn + c1 (Xn - Xp) +
+// c2 (Xp - Xpp), c1 = S[slot1], c2 = S[slot2] of the instance, 0 at the constrained
+// nodes; with both factors 0 it copies Xn (the older levels are then not read).
+// Bound by its launch on small grids and by its 5 to 8 vectors on large ones.  As
+// four launches (combine, mask, guess, dot) 17 us on 16^3 nodes with the gaps
+// between them, now 5.
+template <bool COMBINE>
+__global__ __launch_bounds__(VB) void k_rhs_finish(const Chunk *__restrict__ chunks, const double *S,
+                                                   const OpDev *__restrict__ ops, const double *b0,
+                                                   const double *__restrict__ y, const double *__restrict__ ld, int slot,
+                                                   double *b, int slot1, int slot2, const double *__restrict__ Xn,
+                                                   const double *__restrict__ Xp, const double *__restrict__ Xpp,
+                                                   double *__restrict__ x, double *__restrict__ partial)
+{
+    __shared__ double sh[4];
+    const Chunk ch = chunks[blockIdx.x];
+    const double *Si = S + (int64_t)ch.inst * NSLOT;
+    const OpDev &o = ops[ch.inst];
+    const double c = Si[slot], c1 = Si[slot1], c2 = Si[slot2];
+    const bool lin = c1 != 0.0 || c2 != 0.0, quad = c2 != 0.0;
+    const Lanes l = chunk_lanes(ch);
+    double bv[EPT], yv[EPT], lv[EPT], a[EPT], p[EPT], q[EPT];
+#pragma unroll
+    for (int u = 0; u < EPT; u++) {
+        bv[u] = b0 ? b0[l.c[u]] : 0.0;
+        if (COMBINE) {
+            yv[u] = y[l.c[u]];
+            lv[u] = ld[l.c[u]];
+        }
+        a[u] = Xn[l.c[u]];
+        p[u] = lin ? Xp[l.c[u]] : 0.0;
+        q[u] = quad ? Xpp[l.c[u]] : 0.0;
+    }
+    double acc = 0.0;
+#pragma unroll
+    for (int u = 0; u < EPT; u++)
+        if (l.in[u]) {
+            const bool con = node_constrained(o, l.e[u] - o.off);
+            double v = a[u];
+            if (lin) v = a[u] + c1 * (a[u] - p[u]);
+            if (quad) v += c2 * (p[u] - q[u]);
+            x[l.e[u]] = con ? 0.0 : v;
+            double bb = COMBINE ? combine_rhs(c, lv[u], bv[u], yv[u]) : bv[u];
+            if (con) bb = 0.0;
+            if (COMBINE || con) b[l.e[u]] = bb;
+            acc += bb * bb;
+        }
+    acc = block_sum(acc, sh);
+    if (threadIdx.x == 0) {
+        partial[2 * blockIdx.x] = acc;
+        partial[2 * blockIdx.x + 1] = 0.0;
+    }
+}
+
+// The start of an inner solve: b = r = S[ic] y, x = 0, partial = b.b as k_dot's (four
+// launches before: 19 us on 16^3 nodes with their gaps, now 5).
+template <typename T>
+__global__ __launch_bounds__(VB) void k_inner_start(const Chunk *__restrict__ chunks, const int32_t *active,
+                                                    const double *S, int ic, const double *__restrict__ y,
+                                                    T *__restrict__ b, T *__restrict__ x, T *__restrict__ r,
+                                                    double *__restrict__ partial)
+{
+    __shared__ double sh[4];
+    CHUNK_PROLOGUE
+    const double c = Si[ic];
+    const Lanes l = chunk_lanes(ch);
+    double yv[EPT];
+#pragma unroll
+    for (int u = 0; u < EPT; u++) yv[u] = y[l.c[u]];
+    double acc = 0.0;
+#pragma unroll
+    for (int u = 0; u < EPT; u++)
+        if (l.in[u]) {
+            const T v = T(c * yv[u]);
+            b[l.e[u]] = v;
+            r[l.e[u]] = v;
+            x[l.e[u]] = T(0);
+            acc += (double)v * (double)v;
+        }
+    acc = block_sum(acc, sh);
+    if (threadIdx.x == 0) {
+        partial[2 * blockIdx.x] = acc;
+        partial[2 * blockIdx.x + 1] = 0.0;
+    }
 }
 
 // z = x + y
@@ -458,13 +514,14 @@ __global__ __launch_bounds__(VB) void k_add(const Chunk *__restrict__ chunks, co
         if (l.in[u]) z[l.e[u]] = xv[u] + yv[u];
 }
 
-// Xpp = Xp, Xp = Xn, Xn = X1 (commit of a step, keeping two older levels)
+// Xpp = Xp, Xp = Xn, Xn = X1 (commit of a step, keeping two older levels), of the
+// field of blockIdx.y
 __global__ __launch_bounds__(VB) void k_shift(const Chunk *__restrict__ chunks, const int32_t *active,
-                                              const double *S, const double *__restrict__ X1,
-                                              double *__restrict__ Xn, double *__restrict__ Xp,
-                                              double *__restrict__ Xpp)
+                                              const double *S, ShiftArgs f)
 {
     CHUNK_PROLOGUE
+    const double *__restrict__ X1 = f.X1[blockIdx.y];
+    double *__restrict__ Xn = f.Xn[blockIdx.y], *__restrict__ Xp = f.Xp[blockIdx.y], *__restrict__ Xpp = f.Xpp[blockIdx.y];
     const Lanes l = chunk_lanes(ch);
     double a[EPT], b[EPT], c[EPT];
 #pragma unroll
@@ -514,6 +571,17 @@ __global__ __launch_bounds__(VB) void k_piezo32(const Chunk *__restrict__ chunks
 }
 
 // ---------------------------------------------------------------- reduce
+// Inner tolerance of a defect-correction solve whose right-hand side is r / ||r||:
+// TOL2 = max(floor2, OTOL2 / (4 ORR))
+__device__ __forceinline__ void inner_tol(double *Si, double orr, double otol2, double floor2)
+{
+    const double rel = orr > 0.0 ? otol2 / orr : 1.0;
+    Si[S_BB] = 1.0;
+    Si[S_TOL2] = fmax(floor2, 0.25 * rel);
+    Si[S_ITER] = 0.0;
+    Si[S_STATUS] = 1.0;
+}
+
 // pre: S_RZ, S_TOL2, S_ITER of the instance, read before the partial sums
 __device__ void scalar_op(int op, int inst, const double *v, const double *pre, double *S, int32_t *active,
                           int maxit, int slot, double aux)
@@ -578,9 +646,39 @@ __device__ void scalar_op(int op, int inst, const double *v, const double *pre, 
         else if (v[0] <= pre[1]) stop(0);
         break;
     }
+    case RED_OTOL:        // v0 = b.b of a field solve; aux = rtol^2
+        Si[S_OBB] = v[0];
+        Si[S_OTOL2] = aux * v[0];
+        Si[S_OSTATUS] = 1;
+        break;
+    case RED_OUTER:       // v0 = |b - A x|^2 of a field solve
+    case RED_OUTER_INNER: {
+        const double rr = v[0], tol2 = Si[S_OTOL2];
+        Si[S_ORR] = rr;
+        Si[S_ONORM] = sqrt(fmax(rr, 0.0));
+        Si[S_OINV] = rr > 0.0 ? 1.0 / sqrt(rr) : 0.0;
+        if (!isfinite(rr)) {
+            Si[S_OSTATUS] = -6;
+            active[inst] = 0;
+        } else if (rr <= tol2) {
+            Si[S_OSTATUS] = 0;
+            active[inst] = 0;
+        } else if (op == RED_OUTER_INNER) {
+            inner_tol(Si, rr, tol2, aux);
+        }
+        break;
+    }
     default:
         break;
     }
+}
+
+__global__ void k_set_inner_tol(int ninst, const int32_t *active, double *S, double floor2)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= ninst || (active && !active[i])) return;
+    double *Si = S + (int64_t)i * NSLOT;
+    inner_tol(Si, Si[S_ORR], Si[S_OTOL2], floor2);
 }
 
 // One block per instance.  The loads that do not depend on each other (the
@@ -704,15 +802,29 @@ __global__ __launch_bounds__(VB) void k_set_slots(SlotBlock b, int beg, int cnt,
 
 template <typename T>
 void vfill(const VecCtx &v, T *y, T val) { k_fill<T><<<GRID>>>(v.chunks, v.active, v.S, y, val); HTS_LAUNCH_CHECK(); }
-void vextrapolate(const VecCtx &v, int slot1, int slot2, const OpDev *ops, const double *Xn, const double *Xp,
-                  const double *Xpp, double *x)
+void vrhs_combine(const VecCtx &v, const double *b0, const double *y, const double *ld, int slot, double *b)
 {
-    k_extrapolate<<<GRID>>>(v.chunks, v.active, v.S, slot1, slot2, ops, Xn, Xp, Xpp, x);
+    k_rhs_combine<<<GRID>>>(v.chunks, v.active, v.S, b0, y, ld, slot, b);
     HTS_LAUNCH_CHECK();
 }
-void vrhs_combine(const VecCtx &v, const double *y, const double *ld, int slot, double *b)
+void vrhs_finish(const VecCtx &v, const OpDev *ops, const double *b0, const double *y, const double *ld, int slot, double *b,
+                 int slot1, int slot2, const double *Xn, const double *Xp, const double *Xpp, double *x, double *partial)
 {
-    k_rhs_combine<<<GRID>>>(v.chunks, v.active, v.S, y, ld, slot, b);
+    if (y) k_rhs_finish<true><<<GRID>>>(v.chunks, v.S, ops, b0, y, ld, slot, b, slot1, slot2, Xn, Xp, Xpp, x, partial);
+    else k_rhs_finish<false><<<GRID>>>(v.chunks, v.S, ops, b, nullptr, nullptr, slot, b, slot1, slot2, Xn, Xp, Xpp, x, partial);
+    HTS_LAUNCH_CHECK();
+}
+template <typename T>
+void vinner_start(const VecCtx &v, const double *y, int ic, T *b, T *x, T *r, double *partial)
+{
+    k_inner_start<T><<<GRID>>>(v.chunks, v.active, v.S, ic, y, b, x, r, partial);
+    HTS_LAUNCH_CHECK();
+}
+template void vinner_start<double>(const VecCtx &, const double *, int, double *, double *, double *, double *);
+template void vinner_start<float>(const VecCtx &, const double *, int, float *, float *, float *, double *);
+void set_inner_tol(int ninst, const int32_t *active, double *S, double floor2, hipStream_t s)
+{
+    k_set_inner_tol<<<dim3((ninst + 63) / 64), dim3(64), 0, s>>>(ninst, active, S, floor2);
     HTS_LAUNCH_CHECK();
 }
 void vadd(const VecCtx &v, const double *x, const double *y, double *z)
@@ -720,9 +832,9 @@ void vadd(const VecCtx &v, const double *x, const double *y, double *z)
     k_add<<<GRID>>>(v.chunks, v.active, v.S, x, y, z);
     HTS_LAUNCH_CHECK();
 }
-void vshift(const VecCtx &v, const double *X1, double *Xn, double *Xp, double *Xpp)
+void vshift(const VecCtx &v, const ShiftArgs &f)
 {
-    k_shift<<<GRID>>>(v.chunks, v.active, v.S, X1, Xn, Xp, Xpp);
+    k_shift<<<dim3((unsigned)v.nchunk, 2), dim3(VB), 0, v.stream>>>(v.chunks, v.active, v.S, f);
     HTS_LAUNCH_CHECK();
 }
 template <typename T>
