@@ -4,7 +4,6 @@
 
 namespace hts {
 
-void gm_begin(int ninst, int32_t *active, double *S, double *g, int mres, int32_t *kdim, hipStream_t s);
 // h1: first projection (j+1 per instance); h2: second projection (j+1) and
 // the squared norm of w after the first projection (entry j+1)
 void gm_solve(int ninst, const int32_t *cyc, int mres, const double *H, const double *g, const int32_t *kdim,

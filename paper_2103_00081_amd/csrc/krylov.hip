@@ -9,34 +9,6 @@ namespace hts {
 
 namespace {
 
-__global__ void k_gm_begin(int ninst, int32_t *active, double *S, double *g, int mres, int32_t *kdim)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ninst) return;
-    double *Si = S + (int64_t)i * NSLOT;
-    Si[S_CYC] = 0.0;
-    if (!active[i]) return;
-    const double rr = Si[S_RR];
-    kdim[i] = 0;
-    if (!isfinite(rr)) {
-        Si[S_STATUS] = -6;
-        active[i] = 0;
-        return;
-    }
-    if (rr <= Si[S_TOL2]) {
-        Si[S_STATUS] = 0;
-        active[i] = 0;
-        return;
-    }
-    Si[S_CYC] = 1.0;
-    const double beta = sqrt(rr);
-    double *gi = g + (int64_t)i * (mres + 1);
-    gi[0] = beta;
-    for (int j = 1; j <= mres; j++) gi[j] = 0.0;
-    Si[S_SCALE] = 1.0 / beta;
-    Si[S_STATUS] = 1;
-}
-
 __global__ void k_gm_solve(int ninst, const int32_t *cyc, int mres, const double *H, const double *g,
                            const int32_t *kdim, double *y)
 {
@@ -168,11 +140,6 @@ void convert_plain(int64_t n, const double *in, float *out, hipStream_t s)
 
 static dim3 g1(int n) { return dim3((n + 63) / 64); }
 
-void gm_begin(int ninst, int32_t *active, double *S, double *g, int mres, int32_t *kdim, hipStream_t s)
-{
-    k_gm_begin<<<g1(ninst), dim3(64), 0, s>>>(ninst, active, S, g, mres, kdim);
-    HTS_LAUNCH_CHECK();
-}
 void gm_solve(int ninst, const int32_t *cyc, int mres, const double *H, const double *g, const int32_t *kdim,
               double *y, hipStream_t s)
 {

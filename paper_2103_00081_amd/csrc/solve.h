@@ -106,7 +106,7 @@ struct Batch {
         RedCtx red{};
     };
     WorkSet ws[2][2][2];
-    bool flags_all = false;    // activate_all set the device flags, nothing has changed them
+    bool flags_all = false;    // the device flags are all set
     bool strips = false;       // kernel choice of the current call (use_strips on entry)
     int zc_force[2][2] = {{0, 0}, {0, 0}};
     int family() const { return kernel_family(m[0], strips); }
@@ -197,8 +197,8 @@ struct Batch {
     ~Batch();
     void build_work(int kind);
     void use_strips(bool allowed);
-    // every device flag set; no launch where this did so last (no set_active and
-    // no solve since)
+    // every device flag set; no launch where this or the end of a field solve did so
+    // last
     void activate_all();
     void make_tables(Tables &t, int field, double dt, bool steady, bool mass_only);
     Tables &apply_tables(int field, double dt, bool steady)

@@ -1475,9 +1475,8 @@ int Batch::cg(const Tables &A, const std::function<void(const T *, T *)> &M, con
     }
     if (hook) cg_hook(reinterpret_cast<const double *>(x), 0);
     M(r, z);
-    vdot<T>(v, r, z, nullptr, partial.p);
+    vdot<T>(v, r, z, nullptr, partial.p, pv);
     vreduce(rch, partial.p, 2, RED_STORE, S_RZ, S.p, active.p, 0, 0.0, nullptr, s);
-    vcopy<T>(v, z, pv);
     if (graphed) {
         // Chunks replayed as graphs with a host check between them: the first
         // chunk as long as the previous solve of this system took, then
@@ -1573,15 +1572,18 @@ void Batch::fgmres(const Tables &A, const std::function<void(const T *, T *)> &M
         EpiArgs<T> ep{};
         ep.b = b;
         ep.partial = partial.p;
-        if (started && cycle == 0) {
-            vreduce(rch, partial.p, 2, RED_STORE, S_RR, S.p, active.p, 0, 0.0, nullptr, s);
-        } else {
-            apply_op<T>(A, EPI_RESID_NORM, true, x, V, ep);
-            vreduce(work_set<T>(A.field).red, partial.p, 1, RED_STORE, S_RR, S.p, active.p, 0, 0.0, nullptr, s);
-        }
         // which instances take part (S_CYC) is read back with the first
         // check of the Arnoldi steps, not on its own
-        gm_begin(n, active.p, S.p, gg.p, mres, gkdim.p, s);
+        ArnArgs a0{};
+        a0.mres = mres;
+        a0.g = gg.p;
+        a0.kdim = gkdim.p;
+        if (started && cycle == 0) {
+            vreduce_gm_begin(rch, partial.p, 2, S.p, active.p, a0, s);
+        } else {
+            apply_op<T>(A, EPI_RESID_NORM, true, x, V, ep);
+            vreduce_gm_begin(work_set<T>(A.field).red, partial.p, 1, S.p, active.p, a0, s);
+        }
         vaxpby<T>(v, 1.0, S_SCALE, V, 0.0, -1, V);
         // one Arnoldi step; every kernel skips instances whose cycle ended
         auto step_j = [&](int j) {
@@ -1855,9 +1857,8 @@ FieldStats Batch::solve_field(int field, Hier *mg, const Tables &A, double *b64,
                 const double ist = hS[(size_t)i * NSLOT + S_STATUS];
                 if (ist == -6.0) st.status[i] = -6;
             }
-        set_active(outer);
-        if (fp32) vadd_scaled<float>(vctx(), 1.0, S_ONORM, x32.p, x64);
-        else vadd_scaled<double>(vctx(), 1.0, S_ONORM, inner_x.p, x64);
+        if (fp32) vadd_scaled<float>(vctx(), 1.0, S_ONORM, x32.p, x64, outer, active.p);
+        else vadd_scaled<double>(vctx(), 1.0, S_ONORM, inner_x.p, x64, outer, active.p);
         bool stop = true;
         for (int i = 0; i < n; i++)
             if (outer[i] && st.status[i] != -6 && st.iters[i] < maxit) stop = false;
@@ -2059,8 +2060,8 @@ FieldStats Batch::solve_pressure(double dt, bool steady_all, const hts_solver_op
     pressure_rhs(H, steady);
     std::vector<int32_t> all(n, 1);
     FieldStats st = solve_field(0, &H, H.ops, b.p, x.p, o, all, nullptr);
-    activate_all();
-    vadd(vctx(false), x.p, g.p, P1.p);
+    vadd(vctx(false), x.p, g.p, P1.p, active.p, n);
+    flags_all = true;
     return st;
 }
 
@@ -2084,8 +2085,8 @@ FieldStats Batch::solve_heat(double dt, const hts_solver_opts &o)
     Hier &H = heat_prec(dt, o);
     heat_rhs(H);
     FieldStats st = solve_field(1, H.multigrid ? &H : nullptr, H.ops, b.p, x.p, o, all, &H);
-    activate_all();
-    vadd(vctx(false), x.p, g.p, T1.p);
+    vadd(vctx(false), x.p, g.p, T1.p, active.p, n);
+    flags_all = true;
     return st;
 }
 

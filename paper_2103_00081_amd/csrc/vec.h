@@ -42,6 +42,7 @@ enum RedOp {
     RED_ARNOLDI = 9,           // FGMRES column update (vreduce_arnoldi)
     RED_OTOL = 10,             // OBB = v0, OTOL2 = aux v0, OSTATUS = 1
     RED_OUTER = 11,            // ORR = v0, its root and inverse root; done if v0 <= OTOL2
+    RED_GM_BEGIN = 13,         // start of an FGMRES cycle (vreduce_gm_begin)
     RED_OUTER_INNER = 12       // and, if not done, the tolerance of the inner solve (set_inner_tol; floor2 = aux)
 };
 
@@ -51,8 +52,9 @@ template <typename T> void vcopy(const VecCtx &v, const T *x, T *y);
 template <typename T> void vaxpby(const VecCtx &v, double a, int ia, const T *x, double b, int ib, T *y);
 // z = c d .* r
 template <typename T> void vjacobi(const VecCtx &v, double c, int ic, const T *d, const T *r, T *z);
-// partial[2 blk] = x.y, partial[2 blk + 1] = x.w (if w)
-template <typename T> void vdot(const VecCtx &v, const T *x, const T *y, const T *w, double *partial);
+// partial[2 blk] = x.y, partial[2 blk + 1] = x.w (if w); c = y (if c)
+template <typename T>
+void vdot(const VecCtx &v, const T *x, const T *y, const T *w, double *partial, T *c = nullptr);
 template <typename T>
 void vcg_update(const VecCtx &v, T *x, T *r, const T *p, const T *q, T *r_old, double *partial);
 template <typename T>
@@ -67,7 +69,9 @@ template <typename T, typename TX>
 void vbasis_update(const VecCtx &v, const T *Z, int64_t ld, const int32_t *kdim, const double *Y, int yld,
                    double scale, int iscale, TX *x);
 template <typename TX, typename TY> void vconvert(const VecCtx &v, double sc, int ic, const TX *x, TY *y);
-template <typename T> void vadd_scaled(const VecCtx &v, double sc, int ic, const T *d, double *x);
+// x += c d, c = sc S[ic] or sc, for the flagged instances; dst (the device flags) = flags
+template <typename T>
+void vadd_scaled(const VecCtx &v, double sc, int ic, const T *d, double *x, const std::vector<int32_t> &flags, int32_t *dst);
 // b = (b0 - y) + S[slot] ld (b0 null: 0)
 void vrhs_combine(const VecCtx &v, const double *b0, const double *y, const double *ld, int slot, double *b);
 // b = (b0 - y) + S[slot] ld (y null: b as it is), 0 at the constrained nodes of ops;
@@ -81,8 +85,8 @@ template <typename T>
 void vinner_start(const VecCtx &v, const double *y, int ic, T *b, T *x, T *r, double *partial);
 // per instance: BB = 1, TOL2 = max(floor2, OTOL2 / (4 ORR)), ITER = 0, STATUS = 1
 void set_inner_tol(int ninst, const int32_t *active, double *S, double floor2, hipStream_t s);
-// z = x + y
-void vadd(const VecCtx &v, const double *x, const double *y, double *z);
+// z = x + y of every instance; set[0 .. n) = 1
+void vadd(const VecCtx &v, const double *x, const double *y, double *z, int32_t *set, int n);
 // time-level shift of both fields: Xpp = Xp, Xp = Xn, Xn = X1
 struct ShiftArgs {
     const double *X1[2];
@@ -125,6 +129,11 @@ void vset_slots(const int *slots, int nslots, const double *const *vals, int n, 
 
 void vreduce(const RedCtx &r, const double *partial, int ncomp, int op, int slot, double *S, int32_t *active,
              int maxit, double aux, double *out, hipStream_t s);
+// reduction of the initial residual's norm and the start of an FGMRES cycle: which
+// instances take part (S_CYC), S_SCALE = 1 / norm, the rhs of the small problem
+// (arn.g, arn.kdim)
+void vreduce_gm_begin(const RedCtx &r, const double *partial, int ncomp, double *S, int32_t *active, const ArnArgs &arn,
+                      hipStream_t s);
 // reduction of the second Gram-Schmidt pass (h2 and |w'|^2, ncomp = j + 2)
 // followed by the Arnoldi column update of each active instance
 void vreduce_arnoldi(const RedCtx &r, const double *partial, int ncomp, double *S, int32_t *active,

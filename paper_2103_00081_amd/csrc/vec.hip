@@ -130,11 +130,11 @@ __global__ __launch_bounds__(VB) void k_jacobi(const Chunk *__restrict__ chunks,
         if (l.in[u]) z[l.e[u]] = a * dv[u] * rv[u];
 }
 
-// partial[blk*2 + 0] = x.y (and partial[blk*2+1] = x.w if w)
+// partial[blk*2 + 0] = x.y (and partial[blk*2+1] = x.w if w); c = y if c
 template <typename T>
 __global__ __launch_bounds__(VB) void k_dot(const Chunk *__restrict__ chunks, const int32_t *active,
                                             const double *S, const T *__restrict__ x, const T *__restrict__ y,
-                                            const T *__restrict__ w, double *partial)
+                                            const T *__restrict__ w, double *partial, T *__restrict__ c)
 {
     __shared__ double sh[4];
     CHUNK_PROLOGUE
@@ -153,6 +153,7 @@ __global__ __launch_bounds__(VB) void k_dot(const Chunk *__restrict__ chunks, co
             const double xe = (double)xv[u];
             a += xe * (double)yv[u];
             if (w) b += xe * (double)wv[u];
+            if (c) c[l.e[u]] = yv[u];
         }
     a = block_sum(a, sh);
     if (w) b = block_sum(b, sh);
@@ -364,13 +365,21 @@ __global__ __launch_bounds__(VB) void k_convert(const Chunk *__restrict__ chunks
         if (l.in[u]) y[l.e[u]] = TY(c * (double)xv[u]);
 }
 
-// x (FP64) += c * d (type T)
+// x (FP64) += c * d (type T).  nf > 0: for the instances flagged in f, whose first nf
+// entries also become the device flags
 template <typename T>
 __global__ __launch_bounds__(VB) void k_add_scaled(const Chunk *__restrict__ chunks, const int32_t *active,
                                                    const double *S, double sc, int ic, const T *__restrict__ d,
-                                                   double *__restrict__ x)
+                                                   double *__restrict__ x, FlagBlock f, int nf, int32_t *dst)
 {
-    CHUNK_PROLOGUE
+    const Chunk ch = chunks[blockIdx.x];
+    if (nf > 0) {
+        if (blockIdx.x == 0 && (int)threadIdx.x < nf) dst[threadIdx.x] = f.v[threadIdx.x];
+        if (!f.v[ch.inst]) return;
+    } else if (!active[ch.inst]) {
+        return;
+    }
+    const double *Si = S + (int64_t)ch.inst * NSLOT;
     const double c = ic >= 0 ? sc * Si[ic] : sc;
     const Lanes l = chunk_lanes(ch);
     T dv[EPT];
@@ -496,12 +505,13 @@ __global__ __launch_bounds__(VB) void k_inner_start(const Chunk *__restrict__ ch
     }
 }
 
-// z = x + y
-__global__ __launch_bounds__(VB) void k_add(const Chunk *__restrict__ chunks, const int32_t *active,
-                                            const double *S, const double *__restrict__ x,
-                                            const double *__restrict__ y, double *__restrict__ z)
+// z = x + y of every instance; the flags set[0 .. n) become 1
+__global__ __launch_bounds__(VB) void k_add(const Chunk *__restrict__ chunks, const double *__restrict__ x,
+                                            const double *__restrict__ y, double *__restrict__ z, int32_t *set, int n)
 {
-    CHUNK_PROLOGUE
+    const Chunk ch = chunks[blockIdx.x];
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < n; i += VB) set[i] = 1;
     const Lanes l = chunk_lanes(ch);
     double xv[EPT], yv[EPT];
 #pragma unroll
@@ -673,6 +683,31 @@ __device__ void scalar_op(int op, int inst, const double *v, const double *pre, 
     }
 }
 
+// Start of an FGMRES cycle of an active instance: rr = |b - A x|^2 (the whole block)
+__device__ __forceinline__ void gm_begin(int i, int32_t *active, double *S, const ArnArgs &A, double rr, double tol2)
+{
+    double *Si = S + (int64_t)i * NSLOT, *gi = A.g + (int64_t)i * (A.mres + 1);
+    const int t = threadIdx.x;
+    if (t >= 1 && t <= A.mres) gi[t] = 0.0;
+    if (t != 0) return;
+    Si[S_RR] = rr;
+    Si[S_CYC] = 0.0;
+    A.kdim[i] = 0;
+    if (!isfinite(rr)) {
+        Si[S_STATUS] = -6;
+        active[i] = 0;
+    } else if (rr <= tol2) {
+        Si[S_STATUS] = 0;
+        active[i] = 0;
+    } else {
+        const double beta = sqrt(rr);
+        Si[S_CYC] = 1.0;
+        gi[0] = beta;
+        Si[S_SCALE] = 1.0 / beta;
+        Si[S_STATUS] = 1;
+    }
+}
+
 __global__ void k_set_inner_tol(int ninst, const int32_t *active, double *S, double floor2)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -735,6 +770,7 @@ __global__ __launch_bounds__(RB) void k_reduce(const double *__restrict__ partia
     }
     __syncthreads();
     if (!on) {   // the same for the whole block
+        if (op == RED_GM_BEGIN && threadIdx.x == 0) S[(int64_t)inst * NSLOT + S_CYC] = 0.0;
         // a CG solve that finds the instance already inactive counts no
         // iteration for it (no stale count from an earlier solve)
         if (op == RED_CG_INIT && threadIdx.x == 0) S[(int64_t)inst * NSLOT + S_ITER] = 0.0;
@@ -745,6 +781,7 @@ __global__ __launch_bounds__(RB) void k_reduce(const double *__restrict__ partia
     // FGMRES: the second-pass coefficients and |w'|^2 go straight into the
     // Arnoldi column update of this instance (the whole block takes part)
     if (op == RED_ARNOLDI) arnoldi_column(inst, active, S, arn, vals, rows, rows + 64, rows + 128);
+    else if (op == RED_GM_BEGIN) gm_begin(inst, active, S, arn, vals[0], pre[1]);
     else if (threadIdx.x == 0) scalar_op(op, inst, vals, pre, S, active, maxit, slot, aux);
 }
 
@@ -827,9 +864,9 @@ void set_inner_tol(int ninst, const int32_t *active, double *S, double floor2, h
     k_set_inner_tol<<<dim3((ninst + 63) / 64), dim3(64), 0, s>>>(ninst, active, S, floor2);
     HTS_LAUNCH_CHECK();
 }
-void vadd(const VecCtx &v, const double *x, const double *y, double *z)
+void vadd(const VecCtx &v, const double *x, const double *y, double *z, int32_t *set, int n)
 {
-    k_add<<<GRID>>>(v.chunks, v.active, v.S, x, y, z);
+    k_add<<<GRID>>>(v.chunks, x, y, z, set, n);
     HTS_LAUNCH_CHECK();
 }
 void vshift(const VecCtx &v, const ShiftArgs &f)
@@ -852,9 +889,9 @@ void vjacobi(const VecCtx &v, double c, int ic, const T *d, const T *r, T *z)
     HTS_LAUNCH_CHECK();
 }
 template <typename T>
-void vdot(const VecCtx &v, const T *x, const T *y, const T *w, double *partial)
+void vdot(const VecCtx &v, const T *x, const T *y, const T *w, double *partial, T *c)
 {
-    k_dot<T><<<GRID>>>(v.chunks, v.active, v.S, x, y, w, partial);
+    k_dot<T><<<GRID>>>(v.chunks, v.active, v.S, x, y, w, partial, c);
     HTS_LAUNCH_CHECK();
 }
 template <typename T>
@@ -911,9 +948,14 @@ void vconvert(const VecCtx &v, double sc, int ic, const TX *x, TY *y)
     HTS_LAUNCH_CHECK();
 }
 template <typename T>
-void vadd_scaled(const VecCtx &v, double sc, int ic, const T *d, double *x)
+void vadd_scaled(const VecCtx &v, double sc, int ic, const T *d, double *x, const std::vector<int32_t> &flags, int32_t *dst)
 {
-    k_add_scaled<T><<<GRID>>>(v.chunks, v.active, v.S, sc, ic, d, x);
+    FlagBlock f{};
+    const int n = (int)flags.size();
+    static_assert(FlagBlock::N <= VB, "one block writes the flags");
+    if (n > FlagBlock::N) vset_flags(flags.data(), n, dst, v.stream);
+    else std::copy(flags.begin(), flags.end(), f.v);
+    k_add_scaled<T><<<GRID>>>(v.chunks, dst, v.S, sc, ic, d, x, f, n > FlagBlock::N ? 0 : n, dst);
     HTS_LAUNCH_CHECK();
 }
 template <typename T>
@@ -935,6 +977,15 @@ void vreduce(const RedCtx &r, const double *partial, int ncomp, int op, int slot
     if (ncomp < 1 || ncomp > 64) throw Error(-1, "vreduce: 1..64 components");
     k_reduce<<<dim3((unsigned)r.nseg), dim3(RB), 0, s>>>(partial, ncomp, r.seg_ptr, r.single, op, slot, S,
                                                           active, maxit, aux, out, ArnArgs{});
+    HTS_LAUNCH_CHECK();
+}
+
+void vreduce_gm_begin(const RedCtx &r, const double *partial, int ncomp, double *S, int32_t *active, const ArnArgs &arn,
+                      hipStream_t s)
+{
+    if (arn.mres >= RB) throw Error(-1, "vreduce_gm_begin: restart length");
+    k_reduce<<<dim3((unsigned)r.nseg), dim3(RB), 0, s>>>(partial, ncomp, r.seg_ptr, r.single, RED_GM_BEGIN, 0, S, active, 0,
+                                                          0.0, nullptr, arn);
     HTS_LAUNCH_CHECK();
 }
 
@@ -1007,7 +1058,7 @@ void vset_slots(const int *slots, int nslots, const double *const *vals, int n, 
     template void vcopy<T>(const VecCtx &, const T *, T *);                                              \
     template void vaxpby<T>(const VecCtx &, double, int, const T *, double, int, T *);                   \
     template void vjacobi<T>(const VecCtx &, double, int, const T *, const T *, T *);                    \
-    template void vdot<T>(const VecCtx &, const T *, const T *, const T *, double *);                    \
+    template void vdot<T>(const VecCtx &, const T *, const T *, const T *, double *, T *);                    \
     template void vcg_update<T>(const VecCtx &, T *, T *, const T *, const T *, T *, double *);          \
     template void vmultidot<T>(const VecCtx &, const T *, int64_t, int, const T *, double *, int);       \
     template void vorth_update<T>(const VecCtx &, const T *, int64_t, int, const double *, int, T *, int, \
@@ -1016,7 +1067,7 @@ void vset_slots(const int *slots, int nslots, const double *const *vals, int n, 
                                            const double *, int, double, int, double *);                 \
     template void vbasis_update<T, float>(const VecCtx &, const T *, int64_t, const int32_t *,           \
                                           const double *, int, double, int, float *);                   \
-    template void vadd_scaled<T>(const VecCtx &, double, int, const T *, double *);                      \
+    template void vadd_scaled<T>(const VecCtx &, double, int, const T *, double *, const std::vector<int32_t> &, int32_t *);                      \
     template void vmask<T>(const VecCtx &, const OpDev *, T *, T);
 INST(double)
 INST(float)
