@@ -20,6 +20,9 @@ ARCH = os.environ.get("HTS_ARCH", "gfx950")
 CFLAGS = [
     "--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # host functions on cache lines: the loop that draws a network's initial weights
+    # took 20 or 34 ms by where the linker put it
+    "-Xarch_host", "-falign-functions=64",
     "-Wall", "-Wno-unused-function", "-Wno-unused-variable",
     "-I" + os.path.join(os.path.dirname(HERE), "include"),
 ]
