@@ -322,11 +322,11 @@ hts_status hts_advance(hts_mesh *const *meshes, int32_t n_instances, int32_t n_s
 /* The same operation as hts_apply_operator (same arguments, layout, result
  * bit for bit) for callers that cannot allocate device memory: code under
  * HIP graph capture, tight serving loops, harnesses that forbid allocation.
- * It calls no allocator: the descriptors, the work list, the heat
- * operator's time slots, line-source coefficients and FP32 piezometric
- * pressure live in one static 40 MiB device array per GPU, held until the
- * process ends (FP32 heat applies need 4 bytes per node of it, so meshes up
- * to about 10 M nodes; larger ones give HTS_ERR_ARG before any device
+ * It calls no allocator: the heat operator's time slots and line-source
+ * coefficients live in one static 40 MiB device array per GPU, held until the
+ * process ends.  Sizes are limited as if it also held a work list and, for
+ * FP32 heat applies, 4 bytes per node (meshes up to about 10 M nodes; larger
+ * ones give HTS_ERR_ARG before any device
  * work).  Every call on a GPU reuses that array: calls that overlap on one
  * GPU (several streams or threads) race and must be serialised by the
  * caller.  The mesh's own derived data must exist: HTS_ERR_STATE if the mesh
