@@ -23,9 +23,10 @@ import sqlite3
 import sys
 
 # operator kernels: k_q1_pressure<T, EPI, ...>, k_q1_heat<T, EPI, ...>,
-# k_q2_apply<T, FIELD, EPI, ...>
+# k_q2_apply<T, FIELD, EPI, ...>, k_q1_strip and k_q2_strip<T, FIELD, EPI, ...>
 _Q1 = re.compile(r"k_q1_(pressure|heat)<(float|double), (\d)")
 _Q2 = re.compile(r"k_q2_apply<(float|double), (\d), (\d)")
+_STRIP = re.compile(r"k_(q[12])_strip<(float|double), (\d), (\d)")
 
 
 def apply_info(name: str):
@@ -38,6 +39,10 @@ def apply_info(name: str):
     if m:
         prec = "FP64" if m.group(1) == "double" else "FP32"
         return "Q2 %s apply %s" % ("pressure" if m.group(2) == "0" else "heat", prec), m.group(3)
+    m = _STRIP.search(name)
+    if m:
+        prec = "FP64" if m.group(2) == "double" else "FP32"
+        return "%s %s apply %s" % (m.group(1).upper(), "pressure" if m.group(3) == "0" else "heat", prec), m.group(4)
     return None
 
 
@@ -140,11 +145,12 @@ def pmc(path: str, copy_mib: float = 0.0) -> str:
 
 
 def kernel_source_hash(root: str) -> str:
-    """First 16 hex digits of the SHA-256 of the Q1 operator sources (the
-    benchmark accepts a counter summary only for the source it was taken on)."""
+    """First 16 hex digits of the SHA-256 of the sources of the Q1 operator
+    applies (the benchmark accepts a counter summary only for the source it was
+    taken on)."""
     import hashlib
     import os
-    src = [os.path.join(root, "paper_2103_00081_amd", "csrc", f) for f in ("op_q1.hip", "dev_util.h", "common.h")]
+    src = [os.path.join(root, "paper_2103_00081_amd", "csrc", f) for f in ("op_q1s.hip", "strip.h", "dev_util.h", "common.h")]
     return hashlib.sha256(b"".join(open(f, "rb").read() for f in src)).hexdigest()[:16]
 
 
@@ -165,9 +171,16 @@ def traffic(fetch_db: str, write_db: str, copy_mib: float) -> str:
         copies = [d for d in per.values() if "k_stream_copy" in d["name"]]
         unit = copy_mib * (1 << 20) / max(max(d["v"] for d in copies), 1e-30)
         out.append("%s: %.4f B per counter unit (copy of %.0f MiB)" % (cname, unit, copy_mib))
+        # the launches of a class at the grid it was last launched with (those
+        # before may be the autotuner's, at other depths)
+        last = {}
+        for did in sorted(per, key=int):
+            info = apply_info(per[did]["name"])
+            if info and info[1] == "0":
+                last[info[0]] = per[did]["grid"]
         for d in per.values():
             info = apply_info(d["name"])
-            if not info or info[1] != "0":
+            if not info or info[1] != "0" or d["grid"] != last[info[0]]:
                 continue
             a = per_class.setdefault(info[0], {}).setdefault(cname, [])
             a.append(d["v"] * unit)
