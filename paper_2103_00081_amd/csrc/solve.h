@@ -129,7 +129,7 @@ struct Batch {
     // set by cg / fgmres on return: no work was queued after their last
     // export, so hexpS still holds the current slots
     bool exported_last = false;
-    DBuf<double> partial, redout, redout2, redout3;
+    DBuf<double> partial;
 
     DBuf<double> Pn, Tn, P1, T1, g, b, x, r, z, pp, q, rold, y, ld0, ld1, inner_b, inner_x;
     DBuf<double> Pp, Tp, Ppp, Tpp;   // previous time levels n-1, n-2 (valid where hist_dt, hist_dt2 > 0)

@@ -383,9 +383,6 @@ std::shared_ptr<Batch> build_batch(const std::vector<hts_mesh *> &ms)
     HTS_HIP(hipHostMalloc((void **)&B->hseq, sizeof(uint32_t) * 64, hipHostMallocCoherent));
     *B->hseq = 0;
     std::memset(B->hS, 0, sizeof(double) * n * NSLOT);
-    B->redout.alloc(al, (size_t)n * 64);
-    B->redout2.alloc(al, (size_t)n * 64);
-    B->redout3.alloc(al, (size_t)n * 64);
 
     B->alias_state = n == 1;
     if (B->alias_state) {
