@@ -26,7 +26,8 @@
 // operator (720 pressure) where the tile kernel has 2600, most of them for the Jacobian at
 // 8 points.  Four waves per block: eight have a seventh of halo rows instead of a third,
 // and take 50.6 us against 52.2 (FP32 heat, 128 x 128 x 64), but 11.9 against 9.0 on
-// 40 x 33 x 21, where a block's layer is a wave's.  Kernel times against k_hex_apply, us,
+// 40 x 33 x 21, where a block's layer is a wave's; two cell rows per wave (197 registers,
+// a seventh of halo rows) 51.0 and 12.2.  Kernel times against k_hex_apply, us,
 // at 128 x 128 x 64 cells | 40 x 33 x 21 | 12 x 10 x 8 (there besides a copy, the forming
 // of the FP32 pressure and a write of flags before each apply, 5 to 15 us):
 //   FP64 pressure   88.4 -> 61.9 | 15.4 -> 9.3 | 14.5 -> 8.4
