@@ -331,6 +331,19 @@ void Batch::use_strips(bool allowed)
     if (ws[strips][0][0].n == 0) build_work(strips);
 }
 
+namespace {
+// Hierarchies and the heat spectrum outlive the call that builds them and serve every
+// mode, so their smoothing intervals are measured with one kernel choice, the tiles:
+// with the choice of the building call, a refined step after an FP64 one would smooth
+// with other numbers than on a fresh mesh.
+struct OnTiles {
+    Batch &b;
+    const bool was;
+    explicit OnTiles(Batch &b_) : b(b_), was(b_.strips) { b.use_strips(false); }
+    ~OnTiles() { b.strips = was; }
+};
+}  // namespace
+
 std::shared_ptr<Batch> build_batch(const std::vector<hts_mesh *> &ms)
 {
     auto B = std::make_shared<Batch>();
@@ -864,6 +877,7 @@ Hier &Batch::pressure_hier(bool steady, double dt, const hts_solver_opts &o)
         hier.erase(lru->first);
         hier_used.erase(lru);
     }
+    const OnTiles tiles(*this);
     auto H = std::make_unique<Hier>();
     H->field = 0;
     H->deg = deg;
@@ -1004,6 +1018,7 @@ Hier &Batch::heat_prec(double dt, const hts_solver_opts &o)
     if (heat && heat->dt == dt && heat->deg_req == deg && heat->multigrid == mg && heat->tensor == tensor)
         return *heat;
     drop_graphs();
+    const OnTiles tiles(*this);
     heat = std::make_unique<Hier>();
     Hier &H = *heat;
     H.field = 1;
