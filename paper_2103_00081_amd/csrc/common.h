@@ -62,7 +62,7 @@ struct LineFlat {
 
 // The same operator for the Q1 strip kernel, by cell: a line through the cell
 // column at (xi, eta) has the element matrix coef (B B^T) x Mz of the bilinear
-// values B at (xi, eta) and the line integrals Mz of a layer.  In scaled Haar
+// values B at (xi, eta) and the line integrals Mz of a layer.  In Haar
 // coordinates (op_q1s.hip) B becomes (1, px, py, px py) / 4 per corner pattern
 // and Mz the symmetric [a b; b d] of the z pair; the 1/16 is in a, b, d.  Lines of
 // one cell column are chained; a block of nz entries per line, zero outside its
@@ -93,6 +93,10 @@ struct OpDev {
     // on the host: mass V / 216, stiffness cs (hy hz / hx) / 36 (and the
     // y, z analogues), convection -cadv V / (8 h_d^2)
     double q1m, q1x, q1y, q1z, q1vx, q1vy, q1vz;
+    // the same for the modes of the Q1 strip kernel (op_q1s.hip), each rounded once: mass
+    // (pressure: times cm) of a mode of n differences, V / 64 / 3^n, and stiffness of mode
+    // i = x + 2 y + 4 z (i > 0), cs times the sum of its axes' (hy hz / hx) 3 / 16, / 3^n
+    double hm[4], hk[8];
     const void *k;             // [ncell] k_c              (T)
     const void *lam;           // [ncell] lambda_c         (T, heat)
     const void *cT;            // [ncell] c_T,c            (T, heat)

@@ -243,8 +243,8 @@ static void build_line_operator(hts_mesh *m)
         LineCell *blk = nullptr;
         if (p == 1) {
             LineCell z{};
-            z.px = std::sqrt(3.0) * (1.0 - 2.0 * xi);
-            z.py = std::sqrt(3.0) * (1.0 - 2.0 * eta);
+            z.px = 1.0 - 2.0 * xi;
+            z.py = 1.0 - 2.0 * eta;
             z.src = sid;
             int32_t &head = lccol[(size_t)cx + (size_t)m->n[0] * cy];
             z.next = head;
@@ -265,8 +265,8 @@ static void build_line_operator(hts_mesh *m)
             if (p == 1) {
                 LineCell &e = blk[sg.cz];
                 e.a += (Mz[0][0] + 2.0 * Mz[0][1] + Mz[1][1]) / 64.0;
-                e.b += std::sqrt(3.0) * (Mz[0][0] - Mz[1][1]) / 64.0;
-                e.d += 3.0 * (Mz[0][0] - 2.0 * Mz[0][1] + Mz[1][1]) / 64.0;
+                e.b += (Mz[0][0] - Mz[1][1]) / 64.0;
+                e.d += (Mz[0][0] - 2.0 * Mz[0][1] + Mz[1][1]) / 64.0;
             }
             for (int az = 0; az < n1; az++)
                 for (int ay = 0; ay < n1; ay++)
@@ -498,6 +498,14 @@ OpDev make_op(const hts_mesh *m, int field, bool fp32, double dt, bool steady, b
         o.q1vx = -cw8 / (o.hx * o.hx);
         o.q1vy = -cw8 / (o.hy * o.hy);
         o.q1vz = -cw8 / (o.hz * o.hz);
+        const long double h[3] = {o.hx, o.hy, o.hz}, v = h[0] * h[1] * h[2], s3[4] = {1.0L, 3.0L, 9.0L, 27.0L};
+        for (int n = 0; n < 4; n++) o.hm[n] = (double)((field == 0 ? o.cm : 1.0) * v / (64.0L * s3[n]));
+        for (int i = 0; i < 8; i++) {
+            long double k = 0.0L;
+            for (int d = 0; d < 3; d++)
+                if (i >> d & 1) k += v / (h[d] * h[d]);
+            o.hk[i] = (double)(0.1875L * o.cs * k / s3[(i & 1) + (i >> 1 & 1) + (i >> 2)]);
+        }
     }
     return o;
 }

@@ -88,7 +88,7 @@ extern "C" hts_status hts_apply_operator_noalloc(hts_mesh *m, hts_field field, h
         const bool fp32 = prec == HTS_FP32;
         const bool steady = field == 0 && (dt <= 0.0 || m->B <= 0.0);
         // The entry point refuses what did not fit its scratch when that held the
-        // descriptors, the tile kernels' work list, the chunk list
+        // descriptors (768 bytes), the tile kernels' work list, the chunk list
         // and the FP32 pressure; the strip kernels need the time slots and line sources
         const int family = kernel_family(m, false);
         int ntx, nty;
@@ -102,7 +102,7 @@ extern "C" hts_status hts_apply_operator_noalloc(hts_mesh *m, hts_field field, h
         const size_t o_S = o;      o += up256(NSLOT * sizeof(double));
         const size_t o_src = o;    o += up256((size_t)std::max(1, nsrc) * sizeof(SrcDev));
         const size_t o_coef = o;   o += up256((size_t)std::max(1, nsrc) * sizeof(double));
-        const size_t need = o + up256(2 * sizeof(OpDev)) + up256((size_t)nwork * sizeof(WorkItem)) +
+        const size_t need = o + 768 + up256((size_t)nwork * sizeof(WorkItem)) +
                             up256((size_t)nchunk * sizeof(Chunk)) + up256((size_t)(nchunk ? m->nnode : 0) * sizeof(float));
         if (need > SCRATCH_BYTES || nwork > INT32_MAX)
             throw Error(HTS_ERR_ARG, "mesh too large for the allocation-free apply: needs " + std::to_string(need) +

@@ -13,15 +13,16 @@
 // Every node value is produced by exactly one lane, as a fixed expression: no
 // atomics, bitwise reproducible, independent of the chunk depth.
 //
-// Cells are evaluated in scaled Haar coordinates: along one axis the pair of node
-// values (v0, v1) becomes (s, d) = (v0 + v1, (v0 - v1) / sqrt 3), and results go
-// back as (s + d / sqrt 3, s - d / sqrt 3); there the unscaled 1D mass
-// [2 1; 1 2] is 3 times the identity, the stiffness [1 -1; -1 1] is diagonal,
-// and the values at the two Gauss points are (s + d) / 2 and (s - d) / 2.  Mass
-// and stiffness are one scaling of the 8 coefficients of a cell, products at the
-// Gauss points have unit weights.  The z pair of a node column is formed once
-// for the four cells around it, the y pairs once for the two cells beside it, and
-// the same on the way back.
+// Cells are evaluated in Haar coordinates: along one axis the pair of node values
+// (v0, v1) becomes (s, d) = (v0 + v1, v0 - v1), and results go back as (s + d, s - d);
+// there the unscaled 1D mass [2 1; 1 2] and stiffness [1 -1; -1 1] are diagonal, (3, 1)
+// and (0, 2), and the interpolation to the two Gauss points is (1, 1 / sqrt 3).  Mass
+// and stiffness are one scaling of the 8 coefficients of a cell, a product at the Gauss
+// points weighs pairs of d with 1/3.  The z pair of a node column is formed once for the
+// four cells around it, the y pairs once for the two cells beside it, and the same on
+// the way back, by sums and differences alone: with d / sqrt 3, where all those weights
+// are 1, each pair is rounded once more on either way, and the error against 64 bits
+// was up to 1.6 (FP64 pressure), 1.9 (FP32) and 1.2 (FP32 heat) times the tiles'.
 //
 // What bounds it: on large grids the streaming of the planes (with the cell
 // arithmetic taken out a 256 x 256 x 128 apply takes 50 us for pressure FP64 and
@@ -56,57 +57,80 @@ namespace hts {
 
 namespace {
 
-constexpr double RSQRT3 = 0.57735026918962576451;
 #pragma clang fp contract(off)
 
-// o += the Gauss-point product of A and v projected back (2D scaled Haar
-// coordinates: 0 ss, 1 ds, 2 sd, 3 dd)
+// differences among the axes of Haar coefficient i (index x + 2y + 4z)
+constexpr int haar_order(int i) { return (i & 1) + (i >> 1 & 1) + (i >> 2); }
+
+// o += 3^n times the Gauss-point product of A and v projected back (2D Haar
+// coordinates: 0 ss, 1 ds, 2 sd, 3 dd; n differences of the result's), t = v / 3,
+// n3 = v[3] / 9
 template <typename T>
-__device__ __forceinline__ void haar_prod2(const T A[4], const T v[4], T &o0, T &o1, T &o2, T &o3)
+__device__ __forceinline__ void haar_prod2(const T A[4], const T v[4], T t1, T t2, T t3, T n3, T &o0, T &o1, T &o2, T &o3)
 {
-    o0 = fma_(A[0], v[0], fma_(A[1], v[1], fma_(A[2], v[2], fma_(A[3], v[3], o0))));
-    o1 = fma_(A[0], v[1], fma_(A[1], v[0], fma_(A[2], v[3], fma_(A[3], v[2], o1))));
-    o2 = fma_(A[0], v[2], fma_(A[2], v[0], fma_(A[1], v[3], fma_(A[3], v[1], o2))));
+    o0 = fma_(A[0], v[0], fma_(A[1], t1, fma_(A[2], t2, fma_(A[3], n3, o0))));
+    o1 = fma_(A[0], v[1], fma_(A[1], v[0], fma_(A[2], t3, fma_(A[3], t2, o1))));
+    o2 = fma_(A[0], v[2], fma_(A[2], v[0], fma_(A[1], t3, fma_(A[3], t1, o2))));
     o3 = fma_(A[0], v[3], fma_(A[1], v[2], fma_(A[2], v[1], fma_(A[3], v[0], o3))));
 }
 
-// eigenvalues of the stiffness part in Haar coordinates (index x + 2y + 4z;
-// that of index 0 is 0) for unit coefficient
+// Mass and stiffness on the Haar coefficients, with the weight 3^-n of a coefficient of
+// n differences.  Of a uniform mesh: factors for unit coefficients, m by n, k by
+// coefficient, each rounded once
 template <typename T>
-struct HaarStiff {
-    T k[8];
-    __device__ __forceinline__ HaarStiff(T x, T y, T z)
+struct HaarDiag {
+    T m[4], k[8];
+    __device__ __forceinline__ explicit HaarDiag(const OpDev &o)
     {
-        k[0] = T(0);
-        k[1] = x; k[2] = y; k[3] = x + y;
-        k[4] = z; k[5] = x + z; k[6] = y + z; k[7] = (x + y) + z;
+#pragma unroll
+        for (int n = 0; n < 4; n++) m[n] = T(o.hm[n]);
+#pragma unroll
+        for (int i = 0; i < 8; i++) k[i] = T(o.hk[i]);
+    }
+    // D: the diagonal of a cell of mass a and stiffness coefficient c
+    __device__ __forceinline__ void of_cell(T a, T c, T D[8]) const
+    {
+        D[0] = a * m[0];
+#pragma unroll
+        for (int i = 1; i < 8; i++) D[i] = fma_(c, k[i], a * m[haar_order(i)]);
     }
 };
-
-// W = the mass and stiffness of a cell on Haar coefficients U: mass a, stiffness
-// coefficient c
+// The same of a graded cell from the parts of its column and of its layer: m0, m1, m2 the
+// mass by n (a third taken once per column in FP64: fl(1/3) is off by half a unit in the
+// last place in every cell), x, y, z a third of the stiffnesses for unit coefficient, c
+// the coefficient
 template <typename T>
-__device__ __forceinline__ void haar_mass_stiff(const T U[8], T a, T c, const HaarStiff<T> &K, T W[8])
+__device__ __forceinline__ void haar_diag_graded(T m0, T m1, T m2, T x, T y, T z, T c, T D[8])
 {
-    W[0] = a * U[0];
-#pragma unroll
-    for (int i = 1; i < 8; i++) W[i] = fma_(c, K.k[i], a) * U[i];
+    const T third = T(1.0 / 3.0), ct = third * c, xy = x + y;
+    D[0] = m0;
+    D[1] = fma_(c, x, m1);
+    D[2] = fma_(c, y, m1);
+    D[4] = fma_(c, z, m1);
+    D[3] = fma_(ct, xy, m2);
+    D[5] = fma_(ct, x + z, m2);
+    D[6] = fma_(ct, y + z, m2);
+    D[7] = third * fma_(ct, xy + z, m2);
 }
 
-// W += sum_q N_a(q) (q_h . grad u)(q) dt c_w V / 8 at the 2 x 2 x 2 Gauss
-// points, q_h = -k (grad P + rho_g e_z): per axis the product of two bilinear
+// sum_q N_a(q) (q_h . grad u)(q) dt c_w V / 8 at the 2 x 2 x 2 Gauss points,
+// q_h = -k (grad P + rho_g e_z): per axis the product of two bilinear
 // fields on the cell's cross-section, both given by Haar coefficients (Q: of P,
 // with the gravity part in the z difference), constant along the axis.  ax, ay,
-// az: -k dt c_w V / (8 h_d^2) times 3 / 16.
+// az: -k dt c_w V / (8 h_d^2) times 1 / 16.  C: without the weights 3^-n; C[7] = 0.
 template <typename T>
-__device__ __forceinline__ void haar_convect(const T U[8], const T Q[8], T ax, T ay, T az, T W[8])
+__device__ __forceinline__ void haar_convect(const T U[8], const T Q[8], T ax, T ay, T az, T C[7])
 {
+    const T third = T(1.0 / 3.0), ninth = T(1.0 / 9.0);
+    const T t3 = U[3] * third, t5 = U[5] * third, t6 = U[6] * third, t7 = U[7] * third, n7 = U[7] * ninth;
+#pragma unroll
+    for (int i = 0; i < 7; i++) C[i] = T(0);
     const T Ax[4] = {ax * Q[1], ax * Q[3], ax * Q[5], ax * Q[7]}, vx[4] = {U[1], U[3], U[5], U[7]};
-    haar_prod2(Ax, vx, W[0], W[2], W[4], W[6]);
+    haar_prod2(Ax, vx, t3, t5, t7, n7, C[0], C[2], C[4], C[6]);
     const T Ay[4] = {ay * Q[2], ay * Q[3], ay * Q[6], ay * Q[7]}, vy[4] = {U[2], U[3], U[6], U[7]};
-    haar_prod2(Ay, vy, W[0], W[1], W[4], W[5]);
+    haar_prod2(Ay, vy, t3, t6, t7, n7, C[0], C[1], C[4], C[5]);
     const T Az[4] = {az * Q[4], az * Q[5], az * Q[6], az * Q[7]}, vz[4] = {U[4], U[5], U[6], U[7]};
-    haar_prod2(Az, vz, W[0], W[1], W[2], W[3]);
+    haar_prod2(Az, vz, t5, t6, t7, n7, C[0], C[1], C[2], C[3]);
 }
 
 // the 8 Haar coefficients of the cell right of this lane's column from the z
@@ -114,13 +138,12 @@ __device__ __forceinline__ void haar_convect(const T U[8], const T Q[8], T ax, T
 template <typename T>
 __device__ __forceinline__ void haar_cell(T s0, T d0, T s1, T d1, T U[8])
 {
-    const T r3 = T(RSQRT3);
-    const T y[4] = {s0 + s1, (s0 - s1) * r3, d0 + d1, (d0 - d1) * r3};
+    const T y[4] = {s0 + s1, s0 - s1, d0 + d1, d0 - d1};
 #pragma unroll
     for (int i = 0; i < 4; i++) {
         const T r = from_right(y[i]);
         U[2 * i] = y[i] + r;
-        U[2 * i + 1] = (y[i] - r) * r3;
+        U[2 * i + 1] = y[i] - r;
     }
 }
 
@@ -144,16 +167,15 @@ struct FluxRow {
 template <typename T>
 __device__ __forceinline__ void flux_cell(const FluxRow<T> &f0, const FluxRow<T> &f1, T yl, T yu, T Q[8])
 {
-    const T r1 = T(RSQRT3), r2 = T(1.0 / 3.0), r3 = T(RSQRT3 / 3.0);
     Q[0] = T(0);
-    Q[1] = (f0.xs + f1.xs) * r1;
-    Q[3] = (f0.xs - f1.xs) * r2;
-    Q[5] = (f0.xd + f1.xd) * r2;
-    Q[7] = (f0.xd - f1.xd) * r3;
+    Q[1] = f0.xs + f1.xs;
+    Q[3] = f0.xs - f1.xs;
+    Q[5] = f0.xd + f1.xd;
+    Q[7] = f0.xd - f1.xd;
     const T ys = yl + yu, yd = yl - yu, z = f0.z + f1.z;
-    Q[2] = (ys + from_right(ys)) * r1;
-    Q[6] = (yd + from_right(yd)) * r2;
-    Q[4] = (z + from_right(z)) * r1;
+    Q[2] = ys + from_right(ys);
+    Q[6] = yd + from_right(yd);
+    Q[4] = z + from_right(z);
 }
 
 // W += the injection lines of a cell (layer L of the blocks from b on): the
@@ -179,7 +201,7 @@ __device__ __forceinline__ void line_cell(const OpDev &o, int b, int L, const T 
 // SOLO: descriptor and work in the arguments; its FP32 heat operator reads the
 // FP64 pressure state and forms the piezometric pressure as k_piezo32 does
 template <typename T, int FIELD, int EPI, bool MASKED, bool GRADED, bool SOLO>
-__global__ __launch_bounds__(64 * Q1S_WAVES) void k_q1_strip(const typename std::conditional<SOLO, Solo, Tabled>::type at,
+__global__ __launch_bounds__(64 * Q1S_WAVES, FIELD == 1 && sizeof(T) == 4 ? 4 : 1) void k_q1_strip(const typename std::conditional<SOLO, Solo, Tabled>::type at,
                                                   const T *__restrict__ X, T *__restrict__ Y, EpiArgs<T> ep)
 {
     constexpr int R = Q1S_ROWS;                               // cell rows of a wave
@@ -258,25 +280,25 @@ __global__ __launch_bounds__(64 * Q1S_WAVES) void k_q1_strip(const typename std:
     }
 
     // ---- factors of the unscaled 1D products (formed in double on the host)
-    const T cm = T(o.cm);
-    const T fm = T(3.375 * o.q1m);
-    const HaarStiff<T> fk(T(6.75 * o.q1x), T(6.75 * o.q1y), T(6.75 * o.q1z));
-    const T vx = T(0.1875 * o.q1vx), vy = T(0.1875 * o.q1vy), vz = T(0.1875 * o.q1vz);
+    const HaarDiag<T> fd(o);
+    const T vx = T(0.0625 * o.q1vx), vy = T(0.0625 * o.q1vy), vz = T(0.0625 * o.q1vz);
     const double rho_g = PIEZO ? 0.0 : o.rho_g;               // 0 where the pressure is piezometric
-    const T pz = T(4.0 * RSQRT3 * rho_g * o.hz);
+    const T pz = T(4.0 * rho_g * o.hz);
     // graded meshes: parts of the cell column's hx, hy per row (times a factor
     // of the layer)
-    const bool graded = GRADED && o.hzs != nullptr;
-    T gxy[GRADED ? R : 1], gyx[GRADED ? R : 1], ga[GRADED ? R : 1];
+    const bool graded = GRADED && (SOLO || o.hzs != nullptr);
+    T gx[GRADED ? R : 1], gy[GRADED ? R : 1], gm[GRADED ? R : 1], gm1[GRADED ? R : 1], gm2[GRADED ? R : 1];
     if (graded) {
         const double hx = o.hxs[x < nx ? x : nx - 1];
 #pragma unroll
         for (int r = 0; r < R; r++) {
             const int J = J0 + r;
             const double hy = o.hys[J < 0 ? 0 : (J < ny ? J : ny - 1)];
-            gyx[r] = T(hy / hx);
-            gxy[r] = T(hx / hy);
-            ga[r] = T(hx * hy);
+            gx[r] = T(hy / hx);
+            gy[r] = T(hx / hy);
+            gm[r] = T(hx * hy * 0.015625);
+            gm1[r] = T(hx * hy / 192.0);
+            gm2[r] = T(hx * hy / 576.0);
         }
     }
     T c0 = T(0), c1 = T(0), c2 = T(0);
@@ -431,68 +453,84 @@ __global__ __launch_bounds__(64 * Q1S_WAVES) void k_q1_strip(const typename std:
                 load_c(L + 1, kn, ln, cn);
             }
             mask_cols(L + 1, up);
-            const T r3 = T(RSQRT3);
             T um = T(0), ux = T(0), uz = T(0), uv = T(0), uw = T(0), g = pz;
             if (graded) {
                 const double hz = o.hzs[L], ihz = o.ihzs[L];
-                um = T(hz / 64.0);
-                ux = T(o.cs * hz * 0.1875);
-                uz = T(o.cs * ihz * 0.1875);
-                uv = T(-o.cadv * (0.1875 * 0.125) * hz);
-                uw = T(-o.cadv * (0.1875 * 0.125) * ihz);
-                g = T(4.0 * RSQRT3 * rho_g * hz);
+                um = T(FIELD == 0 ? o.cm * hz : hz);
+                ux = T(o.cs * 0.0625 * hz);
+                uz = T(o.cs * 12.0 * ihz);
+                uv = T(o.cadv * -0.0078125 * hz);
+                uw = T(o.cadv * -0.5 * ihz);
+                g = T(4.0 * rho_g * hz);
             }
             T v[R];
-            T zs0 = lo[0] + up[0], zd0 = (lo[0] - up[0]) * r3;
+            T zs0 = lo[0] + up[0], zd0 = lo[0] - up[0];
             FluxRow<T> f0;
             if (ADV) f0.set(pl[0], pu[0], xl[0]);
             T s0 = T(0), d0 = T(0), us = T(0), ud = T(0);
 #pragma unroll
             for (int r = 0; r < R; r++) {
-                const T zs1 = lo[r + 1] + up[r + 1], zd1 = (lo[r + 1] - up[r + 1]) * r3;
+                const T zs1 = lo[r + 1] + up[r + 1], zd1 = lo[r + 1] - up[r + 1];
                 T U[8], W[8];
                 haar_cell(zs0, zd0, zs1, zd1, U);
                 zs0 = zs1;
                 zd0 = zd1;
-                T lm = fm;
-                HaarStiff<T> lk = fk;
-                if (graded) {
-                    lm = ga[GRADED ? r : 0] * um;
-                    lk = HaarStiff<T>(gyx[GRADED ? r : 0] * ux, gxy[GRADED ? r : 0] * ux, ga[GRADED ? r : 0] * uz);
-                }
-                if (FIELD == 0) haar_mass_stiff(U, co[r] < cbytes ? cm * lm : T(0), ck[r], lk, W);
-                else haar_mass_stiff(U, cc[r] * lm, cl[r], lk, W);
                 if (ADV) {
                     T Q[8], lvx = vx, lvy = vy, lvz = vz;
                     if (graded) {
-                        lvx = gyx[GRADED ? r : 0] * uv;
-                        lvy = gxy[GRADED ? r : 0] * uv;
-                        lvz = ga[GRADED ? r : 0] * uw;
+                        lvx = gx[GRADED ? r : 0] * uv;
+                        lvy = gy[GRADED ? r : 0] * uv;
+                        lvz = gm[GRADED ? r : 0] * uw;
                     }
                     FluxRow<T> f1;
                     f1.set(pl[ADV ? r + 1 : 0], pu[ADV ? r + 1 : 0], xl[ADV ? r + 1 : 0]);
                     flux_cell(f0, f1, pl[ADV ? r : 0] - pl[ADV ? r + 1 : 0], pu[ADV ? r : 0] - pu[ADV ? r + 1 : 0], Q);
                     Q[4] -= g;
                     f0 = f1;
-                    haar_convect(U, Q, ck[r] * lvx, ck[r] * lvy, ck[r] * lvz, W);
+                    T C[7];
+                    haar_convect(U, Q, ck[r] * lvx, ck[r] * lvy, ck[r] * lvz, C);
+                    W[0] = C[0];
+#pragma unroll
+                    for (int i = 1; i < 7; i++) W[i] = T(haar_order(i) == 1 ? 1.0 / 3.0 : 1.0 / 9.0) * C[i];
+                    W[7] = T(0);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 8; i++) W[i] = T(0);
                 }
                 if (FIELD == 1 && lines) line_cell(o, lb[FIELD ? r : 0], L, U, W);
+                const T ma = FIELD == 0 ? T(co[r] < cbytes ? 1 : 0) : cc[r], st = FIELD == 0 ? ck[r] : cl[r];
+                T D[8];
+                if (graded) {
+                    const int q = GRADED ? r : 0;
+                    haar_diag_graded(ma * (gm[q] * um), ma * (gm1[q] * um), ma * (gm2[q] * um), gx[q] * ux, gy[q] * ux,
+                                     gm1[q] * uz, st, D);
+                } else {
+                    fd.of_cell(ma, st, D);
+                }
                 // back along x (the right-hand part goes to the next lane), then y, z
                 T c[4];
 #pragma unroll
-                for (int i = 0; i < 4; i++)
-                    c[i] = fma_(r3, W[2 * i + 1], W[2 * i]) + from_left(fma_(-r3, W[2 * i + 1], W[2 * i]));
-                const T sl = fma_(r3, c[1], c[0]), dw = fma_(r3, c[3], c[2]);
+                for (int i = 0; i < 4; i++) {
+                    const int a = 2 * i, b = a + 1;
+                    if (FIELD == 0) {
+                        const T t = D[b] * U[b];
+                        c[i] = fma_(D[a], U[a], t) + from_left(fma_(D[a], U[a], -t));
+                    } else {
+                        const T s = fma_(D[a], U[a], W[a]), t = fma_(D[b], U[b], W[b]);
+                        c[i] = (s + t) + from_left(s - t);
+                    }
+                }
+                const T sl = c[0] + c[1], dw = c[2] + c[3];
                 if (r > 0) {
                     const T s = us + sl, d = ud + dw;
-                    v[r] = tc[r] + fma_(r3, d, s);
-                    tc[r] = fma_(-r3, d, s);
+                    v[r] = tc[r] + (s + d);
+                    tc[r] = s - d;
                 } else {
                     s0 = sl;
                     d0 = dw;
                 }
-                us = fma_(-r3, c[1], c[0]);
-                ud = fma_(-r3, c[3], c[2]);
+                us = c[0] - c[1];
+                ud = c[2] - c[3];
             }
             // row 0 is the last wave's row R: the two exchange through LDS (two
             // buffers: a wave is at most one barrier ahead)
@@ -502,8 +540,8 @@ __global__ __launch_bounds__(64 * Q1S_WAVES) void k_q1_strip(const typename std:
             {
                 const int below = wave > 0 ? wave - 1 : 0;
                 const T s = xch[L & 1][below][0][lane] + s0, d = xch[L & 1][below][1][lane] + d0;
-                v[0] = tc[0] + fma_(r3, d, s);
-                tc[0] = fma_(-r3, d, s);
+                v[0] = tc[0] + (s + d);
+                tc[0] = s - d;
             }
             if (L >= kb) epilogue(L, v, lo);
 #pragma unroll
