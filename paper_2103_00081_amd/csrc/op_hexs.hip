@@ -10,17 +10,20 @@
 // that two waves share passes through LDS with one barrier per layer.  Every node value
 // is produced by exactly one lane, as a fixed expression.
 //
-// A trilinear field of a cell is held in scaled Haar modes: along an axis the pair
-// (v0, v1) becomes s = v0 + v1 and t = (v1 - v0) / sqrt 3, so the value at the two Gauss
-// points is (s -+ t) / 2 and the derivative sqrt 3 t.  The modes along z and y are formed
+// A trilinear field of a cell is held in Haar modes: along an axis the pair (v0, v1)
+// becomes s = v0 + v1 and t = v1 - v0, so the value at the two Gauss points is
+// (s -+ t / sqrt 3) / 2 and the derivative t.  The modes along z and y are formed
 // once for the cells beside a column, and values, derivatives and their transposes are
-// signed sums of the 8 modes.  With g, J, C the sums without their factors 1/2 and
-// sqrt 3, every term of a cell has the common factor kappa = (sqrt 3 / 4)^3 / 8: stiffness
-// kappa s, mass kappa m / 64, convection kappa c_adv k / 8.  Coordinates are taken in FP64
-// against the lane's own lower node, so that the FP32 operator rounds differences of a
-// cell's size once; the FP32 pressure is the piezometric one that k_piezo32 forms, against
-// the same node.  Cells outside the mesh are computed on whatever their lanes hold and
-// dropped.
+// sums of the 8 modes with weights 1 / sqrt 3 per t of a value.  With g, J, C the sums
+// without their factors 1/2, every term of a cell has the common factor kappa = 1 / 512:
+// stiffness kappa s, mass kappa m / 64, convection kappa c_adv k / 8.  (With t / sqrt 3 as
+// the mode the weights are signs, but each mode is rounded once more on either way and
+// the error of fl(1 / sqrt 3) enters every entry of J: FP32 pressure was off by 1.3 times
+// as much against 64 bits.)  The modes of the coordinates are formed in FP64 against the
+// lane's own lower node, so that the FP32 operator rounds sums of a cell's size once
+// (formed in FP32 they cost 8 % more error and save 1 us of 44); the FP32 pressure is the
+// piezometric one that k_piezo32 forms, against the same node.  Cells outside the mesh are
+// computed on whatever their lanes hold and dropped.
 //
 // What bounds it: the issue of its instructions, 870 for a cell layer of the FP32 heat
 // operator (720 pressure) where the tile kernel has 2600, most of them for the Jacobian at
@@ -41,7 +44,7 @@ namespace hts {
 namespace {
 
 constexpr double I3 = 0.57735026918962576451;   // 1 / sqrt 3
-constexpr double KAPPA = 0.08118988160479111 / 8.0;   // (sqrt 3 / 4)^3 / 8
+constexpr double KAPPA = 1.0 / 512.0;
 
 __device__ __forceinline__ float recip(float x)
 {
@@ -55,20 +58,33 @@ __device__ __forceinline__ double recip(double x)
     return fma_(fma_(-x, r, 1.0), r, r);
 }
 
+// a / x: as many operations as a recip(x), one rounding less
+__device__ __forceinline__ float quot(float a, float x)
+{
+    const float r = __builtin_amdgcn_rcpf(x), q = a * r;
+    return fma_(fma_(-x, q, a), r, q);
+}
+__device__ __forceinline__ double quot(double a, double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma_(fma_(-x, r, 1.0), r, r);
+    const double q = a * r;
+    return fma_(fma_(-x, q, a), r, q);
+}
+
 // modes of a trilinear field, index x + 2 y + 4 z (0: s, 1: t), from the node pairs
 // (lower, upper) of the two rows of this lane and of the next; shift: what the next
 // lane's values are to be raised by
 template <typename T>
 __device__ __forceinline__ void modes8(T a0, T a1, T b0, T b1, T shift, T (&F)[8])
 {
-    const T i3 = T(I3);
-    const T as = a0 + a1, at = (a1 - a0) * i3, bs = b0 + b1, bt = (b1 - b0) * i3;
-    const T l[4] = {as + bs, (bs - as) * i3, at + bt, (bt - at) * i3};
+    const T as = a0 + a1, at = a1 - a0, bs = b0 + b1, bt = b1 - b0;
+    const T l[4] = {as + bs, bs - as, at + bt, bt - at};
 #pragma unroll
     for (int e = 0; e < 4; e++) {
         const T r = e == 0 ? from_right(l[e]) + shift : from_right(l[e]);
         F[2 * e] = l[e] + r;
-        F[1 + 2 * e] = (r - l[e]) * i3;
+        F[1 + 2 * e] = r - l[e];
     }
 }
 
@@ -76,21 +92,23 @@ __device__ __forceinline__ void modes8(T a0, T a1, T b0, T b1, T shift, T (&F)[8
 template <typename T>
 __device__ __forceinline__ void deriv_z(const T (&F)[8], T (&z)[4])
 {
-    const T a = F[4] - F[5], b = F[4] + F[5], c = F[6] - F[7], d = F[6] + F[7];
-    z[0] = a - c;
-    z[1] = b - d;
-    z[2] = a + c;
-    z[3] = b + d;
+    const T i3 = T(I3);
+    const T a = fma_(-i3, F[5], F[4]), b = fma_(i3, F[5], F[4]), c = fma_(-i3, F[7], F[6]), d = fma_(i3, F[7], F[6]);
+    z[0] = fma_(-i3, c, a);
+    z[1] = fma_(-i3, d, b);
+    z[2] = fma_(i3, c, a);
+    z[3] = fma_(i3, d, b);
 }
 // derivatives along x at qy and along y at qx, on one plane of points
 template <typename T>
 __device__ __forceinline__ void deriv_xy(const T (&F)[8], int qz, T (&x)[2], T (&y)[2])
 {
-    const T ts = qz ? F[1] + F[5] : F[1] - F[5], st = qz ? F[2] + F[6] : F[2] - F[6], tt = qz ? F[3] + F[7] : F[3] - F[7];
-    x[0] = ts - tt;
-    x[1] = ts + tt;
-    y[0] = st - tt;
-    y[1] = st + tt;
+    const T i3 = T(I3), w = qz ? i3 : -i3;
+    const T ts = fma_(w, F[5], F[1]), st = fma_(w, F[6], F[2]), tt = fma_(w, F[7], F[3]);
+    x[0] = fma_(-i3, tt, ts);
+    x[1] = fma_(i3, tt, ts);
+    y[0] = fma_(-i3, tt, st);
+    y[1] = fma_(i3, tt, st);
 }
 
 template <typename T, int FIELD>
@@ -192,8 +210,10 @@ __global__ __launch_bounds__(64 * HEXS_WAVES) void k_hex_strip(const Solo at, co
 #pragma unroll
             for (int d = 0; d < 3; d++) {
                 const double own = lo.c[0][d];
-                modes8(T(0), T(hi.c[0][d] - own), T(lo.c[1][d] - own), T(hi.c[1][d] - own),
-                       T(4) * T(from_right(own) - own), G[d]);
+                double g8[8];
+                modes8(0.0, hi.c[0][d] - own, lo.c[1][d] - own, hi.c[1][d] - own, 4.0 * (from_right(own) - own), g8);
+#pragma unroll
+                for (int i = 0; i < 8; i++) G[d][i] = T(g8[i]);
             }
             modes8(lo.u[0], hi.u[0], lo.u[1], hi.u[1], T(0), U);
             if (ADV) {
@@ -217,6 +237,7 @@ __global__ __launch_bounds__(64 * HEXS_WAVES) void k_hex_strip(const Solo at, co
             }
             __builtin_amdgcn_sched_barrier(0);
             // ---- the 8 Gauss points, one plane at a time
+            const T i3 = T(I3);
             T jz[3][4], gz[4], pz[4];
 #pragma unroll
             for (int d = 0; d < 3; d++) deriv_z(G[d], jz[d]);
@@ -231,13 +252,13 @@ __global__ __launch_bounds__(64 * HEXS_WAVES) void k_hex_strip(const Solo at, co
                 deriv_xy(U, qz, gx, gy);
                 if (ADV) deriv_xy(P, qz, px, py);
                 {
-                    const T ss = qz ? U[0] + U[4] : U[0] - U[4], ts = qz ? U[1] + U[5] : U[1] - U[5];
-                    const T s2 = qz ? U[2] + U[6] : U[2] - U[6], t2 = qz ? U[3] + U[7] : U[3] - U[7];
-                    const T a = ss - ts, b = ss + ts, c = s2 - t2, d = s2 + t2;
-                    uq[0] = a - c;
-                    uq[1] = b - d;
-                    uq[2] = a + c;
-                    uq[3] = b + d;
+                    const T w = qz ? i3 : -i3;
+                    const T ss = fma_(w, U[4], U[0]), ts = fma_(w, U[5], U[1]), s2 = fma_(w, U[6], U[2]), t2 = fma_(w, U[7], U[3]);
+                    const T a = fma_(-i3, ts, ss), b = fma_(i3, ts, ss), c = fma_(-i3, t2, s2), d = fma_(i3, t2, s2);
+                    uq[0] = fma_(-i3, c, a);
+                    uq[1] = fma_(-i3, d, b);
+                    uq[2] = fma_(i3, c, a);
+                    uq[3] = fma_(i3, d, b);
                 }
                 T fx[2] = {T(0), T(0)}, fy[2] = {T(0), T(0)}, mq[4];
 #pragma unroll
@@ -255,7 +276,7 @@ __global__ __launch_bounds__(64 * HEXS_WAVES) void k_hex_strip(const Solo at, co
                     C[2][1] = J[0][2] * J[1][0] - J[0][0] * J[1][2];
                     C[2][2] = J[0][0] * J[1][1] - J[0][1] * J[1][0];
                     const T det = J[0][0] * C[0][0] + J[0][1] * C[0][1] + J[0][2] * C[0][2];
-                    const T idet = recip(det), sc = st * idet;
+                    const T idet = ADV ? recip(det) : T(0), sc = ADV ? st * idet : quot(st, det);
                     T cg[3];
 #pragma unroll
                     for (int i = 0; i < 3; i++) cg[i] = C[i][0] * gx[qy] + C[i][1] * gy[qx] + C[i][2] * gz[q];
@@ -275,7 +296,8 @@ __global__ __launch_bounds__(64 * HEXS_WAVES) void k_hex_strip(const Solo at, co
                 }
                 // onto the modes of the test functions
                 const T a = mq[0] + mq[1], b = mq[1] - mq[0], c = mq[2] + mq[3], d = mq[3] - mq[2];
-                const T v[4] = {a + c, b + d + fx[0] + fx[1], c - a + fy[0] + fy[1], d - b + (fx[1] - fx[0]) + (fy[1] - fy[0])};
+                const T v[4] = {a + c, fma_(i3, b + d, fx[0] + fx[1]), fma_(i3, c - a, fy[0] + fy[1]),
+                                fma_(T(1.0 / 3.0), d - b, i3 * ((fx[1] - fx[0]) + (fy[1] - fy[0])))};
 #pragma unroll
                 for (int i = 0; i < 4; i++) {
                     R[i] += v[i];
@@ -285,31 +307,30 @@ __global__ __launch_bounds__(64 * HEXS_WAVES) void k_hex_strip(const Solo at, co
             }
             {
                 const T a = fz[0] + fz[1], b = fz[1] - fz[0], c = fz[2] + fz[3], d = fz[3] - fz[2];
-                R[4] += a + c;
-                R[5] += b + d;
-                R[6] += c - a;
-                R[7] += d - b;
+                R[4] = fma_(i3, R[4], a + c);
+                R[5] = i3 * (R[5] + (b + d));
+                R[6] = i3 * (R[6] + (c - a));
+                R[7] = i3 * fma_(i3, d - b, R[7]);
             }
 #pragma unroll
             for (int i = 0; i < 8; i++) R[i] = cell ? R[i] : T(0);
             // ---- back along x (the right node's part goes to the next lane), then y
-            const T i3 = T(I3);
             T row[2][2];                                      // [row][z mode]
 #pragma unroll
             for (int z = 0; z < 2; z++) {
                 T l[2];
 #pragma unroll
                 for (int y = 0; y < 2; y++) {
-                    const T s = R[2 * y + 4 * z], t = R[1 + 2 * y + 4 * z] * i3;
+                    const T s = R[2 * y + 4 * z], t = R[1 + 2 * y + 4 * z];
                     l[y] = (s - t) + from_left(s + t);
                 }
-                row[0][z] = l[0] - l[1] * i3;
-                row[1][z] = l[0] + l[1] * i3;
+                row[0][z] = l[0] - l[1];
+                row[1][z] = l[0] + l[1];
                 xch[L & 1][wave][z][lane] = row[1][z];
             }
             __syncthreads();
             const int below = wave > 0 ? wave - 1 : 0;
-            const T zs = row[0][0] + xch[L & 1][below][0][lane], zt = (row[0][1] + xch[L & 1][below][1][lane]) * i3;
+            const T zs = row[0][0] + xch[L & 1][below][0][lane], zt = row[0][1] + xch[L & 1][below][1][lane];
             if (L >= kb) store(L, tc + (zs - zt));
             tc = zs + zt;
         }
