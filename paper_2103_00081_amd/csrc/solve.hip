@@ -1,7 +1,6 @@
 // Batches of instances, the multigrid hierarchy, the Krylov solvers and the
 // backward-Euler time step (Section 2: P^{n+1} from Eq. 3, then T^{n+1}
 // from Eq. 4 with the Darcy flux of P^{n+1}).
-#include <cctype>
 #include <cstdio>
 #include <algorithm>
 #include <chrono>
@@ -12,6 +11,7 @@
 #include "internal.h"
 #include "krylov.h"
 #include "solve.h"
+#include "tune.h"
 
 #include <atomic>
 #include <mutex>
@@ -112,72 +112,18 @@ void Batch::replay(const std::string &name, const std::function<void()> &body)
 }
 
 // ----------------------------------------------------------- tuning cache
-// z-chunk depth per (kernel family, field, precision, node dims), filled by hts_autotune and
-// optionally kept in the JSON file named by HTS_TUNE_CACHE.
-namespace {
-std::map<std::string, int> g_tune;
-bool g_tune_loaded = false;
-
-std::string tune_key(int family, int field, int prec, int NX, int NY, int NZ)
-{
-    char b[96];
-    snprintf(b, sizeof(b), "q%d_f%d_%s_%dx%dx%d", family, field, prec ? "fp32" : "fp64", NX, NY, NZ);
-    return b;
-}
-
-void tune_load()
-{
-    if (g_tune_loaded) return;
-    g_tune_loaded = true;
-    const char *path = getenv("HTS_TUNE_CACHE");
-    if (!path) return;
-    FILE *f = fopen(path, "r");
-    if (!f) return;
-    char key[96];
-    int v;
-    // {"q1_f0_129x129x65": 8, ...}: skip the opening brace first
-    int c0 = fgetc(f);
-    while (c0 != EOF && isspace(c0)) c0 = fgetc(f);
-    if (c0 != '{' && c0 != EOF) ungetc(c0, f);
-    while (fscanf(f, " \"%95[^\"]\" : %d", key, &v) == 2) {
-        g_tune[key] = v;
-        int c = fgetc(f);
-        while (c != EOF && c != ',' && c != '}') c = fgetc(f);
-        if (c == '}' || c == EOF) break;
-    }
-    fclose(f);
-}
-
-void tune_save()
-{
-    const char *path = getenv("HTS_TUNE_CACHE");
-    if (!path) return;
-    FILE *f = fopen(path, "w");
-    if (!f) return;
-    fprintf(f, "{");
-    bool first = true;
-    for (auto &kv : g_tune) {
-        fprintf(f, "%s\n  \"%s\": %d", first ? "" : ",", kv.first.c_str(), kv.second);
-        first = false;
-    }
-    fprintf(f, "\n}\n");
-    fclose(f);
-}
-}  // namespace
+static TuneCache g_tune;
 
 void set_tuned_zc(int family, int field, int prec, int NX, int NY, int NZ, int zc)
 {
-    tune_load();
-    g_tune[tune_key(family, field, prec, NX, NY, NZ)] = zc;
+    g_tune.set(family, field, prec, NX, NY, NZ, zc);
 }
 
-void save_tuning() { tune_save(); }
+void save_tuning() { g_tune.save(); }
 
 int tuned_zc(int family, int field, int prec, int NX, int NY, int NZ)
 {
-    tune_load();
-    auto it = g_tune.find(tune_key(family, field, prec, NX, NY, NZ));
-    return it == g_tune.end() ? 0 : it->second;
+    return g_tune.get(family, field, prec, NX, NY, NZ);
 }
 
 // Strips: Q1S_OWNED of the node columns of the y bands laid end to end (one empty
