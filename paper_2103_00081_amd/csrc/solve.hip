@@ -2286,13 +2286,15 @@ hts_status hts_autotune(hts_mesh *const *meshes, int32_t n)
                     int tx, ty;
                     tile_grid(m, fam, f, pr == 0, tx, ty);
                     const int64_t tiles = (int64_t)tx * ty;
-                    cands.insert(cands.begin(), fam == Q2_STRIP ? q2_strip_depth(tiles, m->N[2], f, pr) : hex_strip_depth(tiles, m->N[2]));
+                    cands.push_back(std::min(m->N[2], fam == Q2_STRIP ? q2_strip_depth(tiles, m->N[2], f, pr)
+                                                                        : hex_strip_depth(tiles, m->N[2])));
                 }
+                std::sort(cands.begin(), cands.end());
                 double best[2] = {1e30, 1e30};
-                int bz[2] = {0, 0};
+                int bz[2] = {0, 0}, slower = 0;
                 std::vector<int> tried;
                 for (int zc : cands) {
-                    if (zc > m->N[2] && bz[0] > 0) break;
+                    if (zc > m->N[2] && bz[0] > 0) break;   // the depths rise
                     // Q2 depths are rounded up to whole cell layers
                     const int eff = zc_for(m, fam, f, 0, 1, zc);
                     if (std::find(tried.begin(), tried.end(), eff) != tried.end()) continue;
@@ -2331,8 +2333,10 @@ hts_status hts_autotune(hts_mesh *const *meshes, int32_t n)
                         std::fprintf(stderr, "[hts] autotune family %d field %d %dx%dx%d z-depth %d: %.2f us FP64, "
                                      "%.2f us FP32\n", fam, f, m->N[0], m->N[1], m->N[2], zc,
                                      1000.0 / 6 * ms[0], 1000.0 / 6 * ms[1]);
-                    // deeper ones only get slower once both are well off their best
-                    if (ms[0] > 1.6 * best[0] && ms[1] > 1.6 * best[1]) break;
+                    // past the best depths deeper ones only get slower: two in a row (one
+                    // may be a slow sample) with both precisions well off their best
+                    slower = ms[0] > 1.6 * best[0] && ms[1] > 1.6 * best[1] ? slower + 1 : 0;
+                    if (slower == 2) break;
                     for (int pr = 0; pr < 2; pr++)
                         if (ms[pr] < best[pr]) {
                             best[pr] = ms[pr];
