@@ -87,9 +87,10 @@ extern "C" hts_status hts_apply_operator_noalloc(hts_mesh *m, hts_field field, h
         const hipStream_t s = m->stream;
         const bool fp32 = prec == HTS_FP32;
         const bool steady = field == 0 && (dt <= 0.0 || m->B <= 0.0);
-        // The entry point refuses what did not fit its scratch when that held the
-        // descriptors (768 bytes), the tile kernels' work list, the chunk list
-        // and the FP32 pressure; the strip kernels need the time slots and line sources
+        // What a call needs is the time slots and line sources.  The limit on sizes is an
+        // older one and part of the interface (callers size their meshes by it): two
+        // descriptors (768 bytes), the tile kernels' work list, the chunk list and an FP32
+        // pressure have to fit the scratch as well
         const int family = kernel_family(m, false);
         int ntx, nty;
         tile_grid(m, family, field, !fp32, ntx, nty);
@@ -113,19 +114,17 @@ extern "C" hts_status hts_apply_operator_noalloc(hts_mesh *m, hts_field field, h
         SrcDev *srcs = reinterpret_cast<SrcDev *>(base + o_src);
         double *coef = reinterpret_cast<double *>(base + o_coef);
 
-        if (field == 1) {
+        if (nsrc > 0) {
             // time slots of instance 0, then the line-source coefficients at t + dt
             double hS[NSLOT];
             for (int i = 0; i < NSLOT; i++) hS[i] = 0.0;
             hS[S_TNEW] = m->t + dt;
             hS[S_FSCALE] = dt;
             put(base + o_S, hS, sizeof(hS), s);
-            if (nsrc > 0) {
-                std::vector<SrcDev> ls(m->line_srcs);
-                for (SrcDev &sd : ls) sd.inst = 0;
-                put(base + o_src, ls.data(), ls.size() * sizeof(SrcDev), s);
-                launch_source_values(srcs, nsrc, S, coef, s);
-            }
+            std::vector<SrcDev> ls(m->line_srcs);
+            for (SrcDev &sd : ls) sd.inst = 0;
+            put(base + o_src, ls.data(), ls.size() * sizeof(SrcDev), s);
+            launch_source_values(srcs, nsrc, S, coef, s);
         }
         // one launch, as hts_apply_operator
         const int strip = apply_family(m);
