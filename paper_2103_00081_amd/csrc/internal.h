@@ -176,6 +176,7 @@ struct hts_mesh {
     // with convection, imaginary extent; dt 0: none.  Reused by any batch
     // that builds the heat preconditioner for the same dt.
     double heat_spec[4] = {0.0, 0.0, 0.0, 0.0};
+    int apply_zc[2][2] = {{0, 0}, {0, 0}};   // depth of single applies by field and precision (apply_depth); 0: not looked up
 
     // derived device data (rebuilt when dirty)
     bool dirty = true;
@@ -234,6 +235,9 @@ void tile_grid(const hts_mesh *m, int family, int field, bool fp64, int &ntx, in
 // zc per block
 template <typename T>
 void launch_strip_solo(const hts_mesh *m, int field, const OpDev &op, int zc, const T *x, T *y, hipStream_t s);
+// node planes per block of a single apply: looked up on the mesh's first one (the rule of
+// the Q2 strips goes through all depths) and again after the mesh is tuned
+int apply_depth(hts_mesh *m, int field, bool fp32);
 // node planes per work item of the operator kernels (force > 0: that depth)
 int zc_for(const hts_mesh *M, int family, int field, int prec, int64_t tiles, int force);
 

@@ -127,10 +127,7 @@ extern "C" hts_status hts_apply_operator_noalloc(hts_mesh *m, hts_field field, h
             launch_source_values(srcs, nsrc, S, coef, s);
         }
         // one launch, as hts_apply_operator
-        const int strip = apply_family(m);
-        int sx, sy;
-        tile_grid(m, strip, field, !fp32, sx, sy);
-        const int szc = zc_for(m, strip, field, fp32 ? 1 : 0, (int64_t)sx * sy, 0);
+        const int szc = apply_depth(m, field, fp32);
         OpDev op = make_op(m, field, fp32, dt, steady, false);
         op.P = m->P.p;
         op.lcoef = coef;

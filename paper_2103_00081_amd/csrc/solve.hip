@@ -222,6 +222,18 @@ int zc_for(const hts_mesh *M, int family, int field, int prec, int64_t tiles, in
     return fit((int)z);
 }
 
+int apply_depth(hts_mesh *m, int field, bool fp32)
+{
+    int &zc = m->apply_zc[field][fp32];
+    if (zc == 0) {
+        const int family = apply_family(m);
+        int ntx, nty;
+        tile_grid(m, family, field, !fp32, ntx, nty);
+        zc = zc_for(m, family, field, fp32, (int64_t)ntx * nty, 0);
+    }
+    return zc;
+}
+
 // Work lists of the kernel choice `kind` (their blocks depend on the tuning)
 void Batch::build_work(int kind)
 {
@@ -2139,6 +2151,7 @@ std::shared_ptr<Batch> multi_batch(const std::vector<hts_mesh *> &ms)
 void forget_batches(hts_mesh *m)
 {
     m->batches.clear();
+    for (auto &z : m->apply_zc) z[0] = z[1] = 0;
     std::vector<std::shared_ptr<Batch>> drop;
     {
         std::lock_guard<std::mutex> lk(g_multi_mu);
@@ -2233,10 +2246,7 @@ hts_status hts_apply_operator(hts_mesh *m, hts_field field, hts_precision prec, 
         OpDev o = make_op(m, field, fp32, dt, steady, false);
         o.P = m->P.p;
         o.lcoef = b.lcoef.p;
-        const int family = apply_family(m);
-        int ntx, nty;
-        tile_grid(m, family, field, !fp32, ntx, nty);
-        const int zc = zc_for(m, family, field, fp32, (int64_t)ntx * nty, 0);
+        const int zc = apply_depth(m, field, fp32);
         b.timed_apply(field, EPI_STORE, fp32, [&] {
             if (fp32) launch_strip_solo<float>(m, field, o, zc, (const float *)x_dev, (float *)y_dev, b.s);
             else launch_strip_solo<double>(m, field, o, zc, (const double *)x_dev, (double *)y_dev, b.s);
