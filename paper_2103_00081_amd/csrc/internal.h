@@ -217,9 +217,10 @@ void forget_batches(hts_mesh *m);               // drop every cached batch that 
 bool is_constrained(const hts_mesh *m, int field, int i, int j, int k);   // host, after prepare_mesh
 OpDev make_op(const hts_mesh *m, int field, bool fp32, double dt, bool steady, bool mass_only);
 // Kernel family of a mesh.  strips: the family for callers whose results may
-// round differently from earlier ones.  The refined mode keeps the tile kernels:
-// its FP32 Krylov solves turn a last-bit change of an operator into 1e-9 of T
-// (whose tolerance is 1e-8), and its time steps stay the same bit for bit.
+// round differently from those of the tiles.  The refined mode, the harvest of training
+// pairs and all that is measured for the smoothers keep the tile kernels: the refined
+// mode's FP32 Krylov solves turn a last-bit change of an operator into 1e-9 of T (its
+// tolerance is 1e-8).
 inline int kernel_family(const hts_mesh *m, bool strips)
 {
     if (m->general) return DEGREE_HEX;

@@ -744,7 +744,7 @@ hts_status hts_nn_harvest(hts_nn *nn, hts_mesh *const *meshes, int32_t n_draws, 
                 nn->dnfree.push_back(nfree);
             }
             auto Bp = solo_batch(m);
-            Bp->use_strips(false);   // the pairs stay the same bit for bit
+            Bp->use_strips(false);   // the same pairs whichever mode ran before
             Batch &B = *Bp;
             B.gather_state();
             const double t0 = m->t;

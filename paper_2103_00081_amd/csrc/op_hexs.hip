@@ -25,7 +25,8 @@
 // piezometric one that k_piezo32 forms, against the same node.  Cells outside the mesh are
 // computed on whatever their lanes hold and dropped.
 //
-// What bounds it: the issue of its instructions, 870 for a cell layer of the FP32 heat
+// What bounds it: the issue of its instructions (a vector instruction in 93 to 100 % of the
+// busy time in FP32, 74 % in FP64), 815 for a cell layer of the FP32 heat
 // operator (720 pressure) where the tile kernel has 2600, most of them for the Jacobian at
 // 8 points.  Four waves per block: eight have a seventh of halo rows instead of a third,
 // and take 50.6 us against 52.2 (FP32 heat, 128 x 128 x 64), but 11.9 against 9.0 on
@@ -33,10 +34,12 @@
 // a seventh of halo rows) 51.0 and 12.2.  Kernel times against k_hex_apply, us,
 // at 128 x 128 x 64 cells | 40 x 33 x 21 | 12 x 10 x 8 (there besides a copy, the forming
 // of the FP32 pressure and a write of flags before each apply, 5 to 15 us):
-//   FP64 pressure   88.4 -> 61.9 | 15.4 -> 9.3 | 14.5 -> 8.4
-//   FP32 pressure   62.5 -> 45.1 | 15.4 -> 8.7 | 14.1 -> 8.8
-//   FP64 heat      144.1 -> 67.9 | 20.0 -> 9.7 | 18.3 -> 9.3
-//   FP32 heat       79.5 -> 50.9 | 19.0 -> 9.2 | 17.9 -> 9.0
+//   FP64 pressure   87.7 -> 61.4 | 15.3 -> 8.8 | 14.3 -> 8.3
+//   FP32 pressure   61.7 -> 43.6 | 15.1 -> 8.5 | 14.2 -> 8.2
+//   FP64 heat      142.9 -> 70.6 | 20.0 -> 10.0 | 18.8 -> 9.1
+//   FP32 heat       81.3 -> 50.5 | 19.0 -> 9.1 | 17.0 -> 8.9
+// The solves on hexahedra keep the tile kernel: this one has the store epilogue alone, and
+// no form over device tables.
 #include "strip.h"
 
 namespace hts {

@@ -26,21 +26,26 @@
 //
 // What bounds it: on large grids the streaming of the planes (with the cell
 // arithmetic taken out a 256 x 256 x 128 apply takes 50 us for pressure FP64 and
-// 55 us for heat FP32 where the whole kernels take 56 and 65), on small ones the
+// 55 us for heat FP32), on small ones the
 // march of a wave.  Against the LDS tiles of op_q1.hip on 256 x 256 x 128 cells
-// (four rotating buffer pairs, events around each launch): pressure FP64 78.7 ->
-// 55.9 us, FP32 50.5 -> 34.1, heat FP64 149 -> 119, FP32 86.4 -> 64.6; on
-// 128 x 128 x 64: 17.6 -> 14.5, 14.3 -> 11.4, 28.7 -> 23.3, 21.1 -> 18.1.  Two
-// cell rows per wave: with four the same at 256 x 256 x 128 (54.9, 35.7, 116, 70)
+// (four rotating buffer pairs, events around each launch): pressure FP64 78.3 ->
+// 54.5 us, FP32 50.6 -> 34.4, heat FP64 153 -> 117, FP32 89.9 -> 70.0; on
+// 128 x 128 x 64: 17.3 -> 13.0, 14.0 -> 10.3, 28.3 -> 22.1, 21.0 -> 17.3; on
+// 256 x 200 x 128 graded: 68.0 -> 51.6, 44.5 -> 33.4, 135 -> 113, 82.3 -> 68.2.  Two
+// cell rows per wave: with four (as scaled pairs) the same at 256 x 256 x 128
 // and slower on small grids (48^3 heat FP32 9.5 -> 11.7 us); with one, 8 to 40 %
 // slower on the large grid.  Waves side by side share a halo row; on their own
-// (four rows each) heat FP32 takes 80 us.
+// (four rows each) heat FP32 takes 80 us.  A block's layer costs the same however few of
+// its columns the mesh has: heat on columns of at most 8 x 8 cells and 8000 or more
+// layers takes 1.05 to 1.6 times the tiles (2 x 2 x 30000: FP64 70 -> 109 us).
 //
 // One apply of one mesh (SOLO) takes its descriptor by value, finds its work from
 // the block index and reads the pressure state itself: 32^3 pressure FP32 8.5 ->
-// 5.0 us a call, 128 x 128 x 64 heat FP64 31.7 -> 18.6 (flag, slot and pressure
-// copies before it), 256 x 256 x 128 heat FP32 113 -> 69 (and no FP32 copy of the
-// pressure).
+// 4.7 us a call, 128 x 128 x 64 heat FP64 31.7 -> 18.6 (flag, slot and pressure
+// copies before it), 256 x 256 x 128 heat FP32 113 -> 68 (and no FP32 copy of the
+// pressure).  A SOLO kernel for graded meshes never sees a uniform one, whose factors
+// would take 26 to 43 registers and scalar spills from it: 256 x 200 x 128 heat FP64
+// 120 -> 108 us, FP32 74.9 -> 62.6.
 //
 // Fused multiply-adds are written out and contraction is off, so that every
 // instance of the kernel (graded or not, each epilogue) rounds alike.
@@ -284,8 +289,8 @@ __global__ __launch_bounds__(64 * Q1S_WAVES, FIELD == 1 && sizeof(T) == 4 ? 4 : 
     const T vx = T(0.0625 * o.q1vx), vy = T(0.0625 * o.q1vy), vz = T(0.0625 * o.q1vz);
     const double rho_g = PIEZO ? 0.0 : o.rho_g;               // 0 where the pressure is piezometric
     const T pz = T(4.0 * rho_g * o.hz);
-    // graded meshes: parts of the cell column's hx, hy per row (times a factor
-    // of the layer)
+    // graded meshes (in a batch some may be uniform): parts of the cell column's hx, hy
+    // per row (times a factor of the layer)
     const bool graded = GRADED && (SOLO || o.hzs != nullptr);
     T gx[GRADED ? R : 1], gy[GRADED ? R : 1], gm[GRADED ? R : 1], gm1[GRADED ? R : 1], gm2[GRADED ? R : 1];
     if (graded) {

@@ -1,4 +1,4 @@
-// Shared by the strip kernels (op_q1s.hip, op_q2s.hip): raw buffer access, lane
+// Shared by the strip kernels (op_q1s.hip, op_q2s.hip, op_hexs.hip): raw buffer access, lane
 // shifts, and where a launch finds its work.
 #pragma once
 #include <type_traits>

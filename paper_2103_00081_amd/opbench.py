@@ -1,11 +1,12 @@
 """Time the matrix-free operator kernels on the energy-pile field meshes.
 
 Usage:
-  python -m paper_2103_00081_amd.opbench [--degree 1|2] [--classes f,p;...]
+  python -m paper_2103_00081_amd.opbench [--degree 1|2 | --hex] [--classes f,p;...]
          [--reps N] [--copy-mib M]
 
 Builds the 256x256x128 Q1 (or 128x128x64 Q2) pile-field mesh (8,520,321
-nodes per field), picks the tile depth with hts_autotune, then applies each
+nodes per field) or, with --hex, the 128x128x64 layered aquifer on terrain-following
+hexahedra, picks the tile depth with hts_autotune, then applies each
 requested operator class (field 0 pressure / 1 heat, precision 0 FP64 / 1
 FP32) `reps` times, cycling four (x, y) buffer pairs so that every apply
 streams from HBM past the 256 MB last-level cache, and prints one line per
@@ -28,6 +29,7 @@ def main(argv=None):
     ap.add_argument("--reps", type=int, default=40)
     ap.add_argument("--copy-mib", type=int, default=0)
     ap.add_argument("--ncells", default=None)
+    ap.add_argument("--hex", action="store_true")
     a = ap.parse_args(argv)
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     if root not in sys.path:
@@ -44,7 +46,10 @@ def main(argv=None):
         print("copy %d MiB: %.2f us, %.1f GB/s" % (a.copy_mib, 1e3 * ms, 2 * n * 4 / (ms * 1e-3) / 1e9), flush=True)
         del src, dst
     nc = tuple(int(v) for v in a.ncells.split(",")) if a.ncells else None
-    scn = synth.config3(degree=a.degree, ncells=nc, n_steps=1)
+    if a.hex:
+        scn = synth.aquifer_hex(ncells=nc or (128, 128, 64), n_steps=1)
+    else:
+        scn = synth.config3(degree=a.degree, ncells=nc, n_steps=1)
     m = hts.from_scenario(scn, initial=False)
     hts.autotune([m])
     n = m.nnode
@@ -64,8 +69,8 @@ def main(argv=None):
             m.apply_operator(field, prec, scn.dt, xs[r % 4], ys[r % 4])
         torch.cuda.synchronize()
         k = hts.kernel_timing_stop()[(field, prec)]
-        print("Q%d field %d prec %d nodes %d: %.2f us per launch (%d launches)"
-              % (a.degree, field, prec, n, 1e3 * k["ms"] / k["launches"], k["launches"]), flush=True)
+        print("%s field %d prec %d nodes %d: %.2f us per launch (%d launches)"
+              % ("hexahedra" if a.hex else "Q%d" % a.degree, field, prec, n, 1e3 * k["ms"] / k["launches"], k["launches"]), flush=True)
         del xs, ys
 
 

@@ -10,6 +10,12 @@ Usage:
       the store epilogue, scaled by the counts of the library's plain copy of
       copy_mib MiB, with the hash of the operator sources they were taken on
       (the lines the benchmark reads).
+  python -m paper_2103_00081_amd.profsummary issue <results.db>
+      of a run that collected SQ_WAVES SQ_INSTS_VALU SQ_INSTS_SALU SQ_ACTIVE_INST_VALU
+      SQ_WAVE_CYCLES SQ_WAIT_ANY SQ_BUSY_CU_CYCLES: per operator class with the store
+      epilogue, at the grid it was last launched with, instructions per wave, the share
+      of the busy SIMD time in which a vector instruction is issued, waves per busy SIMD
+      and the share of the waves' time spent waiting.
   python -m paper_2103_00081_amd.profsummary pmc <counter_collection.csv | results.db> [copy_mib]
       per-dispatch hardware counters (e.g. FETCH_SIZE, WRITE_SIZE) averaged
       per operator class, epilogue and grid size; with copy_mib, the counters
@@ -23,10 +29,11 @@ import sqlite3
 import sys
 
 # operator kernels: k_q1_pressure<T, EPI, ...>, k_q1_heat<T, EPI, ...>,
-# k_q2_apply<T, FIELD, EPI, ...>, k_q1_strip and k_q2_strip<T, FIELD, EPI, ...>
+# k_q2_apply and k_hex_apply<T, FIELD, EPI, ...>, k_q1_strip and k_q2_strip<T, FIELD,
+# EPI, ...>, k_hex_strip<T, FIELD> (the store epilogue)
 _Q1 = re.compile(r"k_q1_(pressure|heat)<(float|double), (\d)")
-_Q2 = re.compile(r"k_q2_apply<(float|double), (\d), (\d)")
-_STRIP = re.compile(r"k_(q[12])_strip<(float|double), (\d), (\d)")
+_CELLS = re.compile(r"k_(q2|hex)_apply<(float|double), (\d), (\d)")
+_STRIP = re.compile(r"k_(q[12]|hex)_strip<(float|double), (\d)(?:, (\d))?")
 
 
 def apply_info(name: str):
@@ -35,14 +42,11 @@ def apply_info(name: str):
     if m:
         prec = "FP64" if m.group(2) == "double" else "FP32"
         return "Q1 %s apply %s" % (m.group(1), prec), m.group(3)
-    m = _Q2.search(name)
-    if m:
-        prec = "FP64" if m.group(1) == "double" else "FP32"
-        return "Q2 %s apply %s" % ("pressure" if m.group(2) == "0" else "heat", prec), m.group(3)
-    m = _STRIP.search(name)
+    m = _CELLS.search(name) or _STRIP.search(name)
     if m:
         prec = "FP64" if m.group(2) == "double" else "FP32"
-        return "%s %s apply %s" % (m.group(1).upper(), "pressure" if m.group(3) == "0" else "heat", prec), m.group(4)
+        cells = "hexahedra" if m.group(1) == "hex" else m.group(1).upper()
+        return "%s %s apply %s" % (cells, "pressure" if m.group(3) == "0" else "heat", prec), m.group(4) or "0"
     return None
 
 
@@ -199,11 +203,40 @@ def traffic(fetch_db: str, write_db: str, copy_mib: float) -> str:
     return "\n".join(out)
 
 
+def issue(path: str) -> str:
+    """Issue counters of the operator applies (see the module docstring)."""
+    per, last, acc = {}, {}, {}
+    for did, name, grid, cn, v in _pmc_rows(path):
+        info = apply_info(name)
+        if info and info[1] == "0":
+            d = per.setdefault(did, {"class": info[0], "grid": grid})
+            d[cn] = d.get(cn, 0.0) + float(v)
+    for did in sorted(per, key=int):
+        last[per[did]["class"]] = per[did]["grid"]
+    for d in per.values():
+        if d["grid"] == last[d["class"]]:
+            a = acc.setdefault(d["class"], {"n": 0})
+            a["n"] += 1
+            for k, v in d.items():
+                if k not in ("class", "grid"):
+                    a[k] = a.get(k, 0.0) + v
+    out = ["| class | launches | waves | VALU per wave | SALU per wave | VALU issued, of busy SIMD time | waves per busy SIMD | "
+           "waiting, of wave time |", "|---|---|---|---|---|---|---|---|"]
+    for k, a in sorted(acc.items()):
+        w, busy, wave = a["SQ_WAVES"], a["SQ_BUSY_CU_CYCLES"], a["SQ_WAVE_CYCLES"]
+        out.append("| %s | %d | %.0f | %.0f | %.0f | %.0f%% | %.1f | %.0f%% |" % (
+            k, a["n"], w / a["n"], a["SQ_INSTS_VALU"] / w, a["SQ_INSTS_SALU"] / w, 100 * a["SQ_ACTIVE_INST_VALU"] / busy,
+            wave / busy, 100 * a["SQ_WAIT_ANY"] / wave))
+    return "\n".join(out)
+
+
 if __name__ == "__main__":
     if len(sys.argv) >= 3 and sys.argv[1] == "pmc":
         print(pmc(sys.argv[2], float(sys.argv[3]) if len(sys.argv) > 3 else 0.0))
     elif len(sys.argv) >= 5 and sys.argv[1] == "traffic":
         print(traffic(sys.argv[2], sys.argv[3], float(sys.argv[4])))
+    elif len(sys.argv) >= 3 and sys.argv[1] == "issue":
+        print(issue(sys.argv[2]))
     elif len(sys.argv) >= 3 and sys.argv[1] == "trace":
         print(summarise(sys.argv[2], int(sys.argv[3]) if len(sys.argv) > 3 else 40))
     else:
