@@ -5,6 +5,8 @@ thread sanitizer, which ends it with an error at the first unlocked access."""
 import os
 import subprocess
 
+import pytest
+
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2103_00081_amd", "csrc")
 
 PROGRAM = r"""
@@ -43,6 +45,8 @@ def test_lookups_while_another_mesh_is_tuned(tmp_path):
     subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=thread", "-I", CSRC, src, "-o", exe, "-pthread"], check=True)
     env = dict(os.environ, HTS_TUNE_CACHE=cache, TSAN_OPTIONS="halt_on_error=1 exitcode=66")
     r = subprocess.run([exe], env=env, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    if "unexpected memory mapping" in r.stdout:      # its shadow does not fit this kernel's address layout
+        pytest.skip("the thread sanitizer cannot run here")
     assert r.returncode == 0 and r.stdout.split() == ["done"], r.stdout[-2000:]
     with open(cache) as f:
         text = f.read()
