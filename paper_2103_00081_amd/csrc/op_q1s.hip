@@ -44,7 +44,7 @@
 // 4.7 us a call, 128 x 128 x 64 heat FP64 31.7 -> 18.6 (flag, slot and pressure
 // copies before it), 256 x 256 x 128 heat FP32 113 -> 68 (and no FP32 copy of the
 // pressure).  A SOLO kernel for graded meshes never sees a uniform one, whose factors
-// would take 26 to 43 registers and scalar spills from it: 256 x 200 x 128 heat FP64
+// would take 9 to 26 registers from it and spill scalar ones: 256 x 200 x 128 heat FP64
 // 120 -> 108 us, FP32 74.9 -> 62.6.
 //
 // Fused multiply-adds are written out and contraction is off, so that every
@@ -122,7 +122,7 @@ __device__ __forceinline__ void haar_diag_graded(T m0, T m1, T m2, T x, T y, T z
 // q_h = -k (grad P + rho_g e_z): per axis the product of two bilinear
 // fields on the cell's cross-section, both given by Haar coefficients (Q: of P,
 // with the gravity part in the z difference), constant along the axis.  ax, ay,
-// az: -k dt c_w V / (8 h_d^2) times 1 / 16.  C: without the weights 3^-n; C[7] = 0.
+// az: -k dt c_w V / (8 h_d^2) times 1 / 16.  C: 3^n times the result (that of index 7 is 0).
 template <typename T>
 __device__ __forceinline__ void haar_convect(const T U[8], const T Q[8], T ax, T ay, T az, T C[7])
 {
@@ -204,7 +204,9 @@ __device__ __forceinline__ void line_cell(const OpDev &o, int b, int L, const T 
 }
 
 // SOLO: descriptor and work in the arguments; its FP32 heat operator reads the
-// FP64 pressure state and forms the piezometric pressure as k_piezo32 does
+// FP64 pressure state and forms the piezometric pressure as k_piezo32 does.  FP32 heat
+// has to fit four waves on a SIMD (at 131 registers, three, a graded 256 x 200 x 128
+// apply took 76.7 us, at 128 72.6)
 template <typename T, int FIELD, int EPI, bool MASKED, bool GRADED, bool SOLO>
 __global__ __launch_bounds__(64 * Q1S_WAVES, FIELD == 1 && sizeof(T) == 4 ? 4 : 1) void k_q1_strip(const typename std::conditional<SOLO, Solo, Tabled>::type at,
                                                   const T *__restrict__ X, T *__restrict__ Y, EpiArgs<T> ep)
